@@ -1216,6 +1216,9 @@ amp_status search_on(amp_index* ix, Workspace& w, const void* queries, int64_t n
       opts->stage_ms[i] = ms;
       total += ms;
     }
+    // (L2 with an exact integer LUT: the bases are computed before the predictor)
+    if (ix->metric == AMP_L2 && pol->kind != AMP_POLICY_FP32 && lut_dtype != AMP_LUT_F8E4M3 && !sd.noskip)
+      std::swap(opts->stage_ms[2], opts->stage_ms[3]);
     opts->stage_ms[NS] = total;
     for (auto& e : ev) hipEventDestroy(e);
   }

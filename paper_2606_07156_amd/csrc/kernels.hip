@@ -602,6 +602,7 @@ struct PairArgs {
   const float* C;
   const int16_t* qi16;    // inner product: queries and centroids on the grid (d' = |qi - ci|^2)
   const int16_t* ci16;
+  const int64_t* dq2_in;  // d' of every pair where the base kernel has computed it (L2), or null
   int64_t* dot_out;       // adaptive inner product: qi.ci of every pair (read in the same pass), or null
   int32_t* ipmask;        // with dot_out: the widths each query's pairs use
   const int32_t* probes;
@@ -720,7 +721,9 @@ __global__ __launch_bounds__(256) void k_pairs(PairArgs a, ModelArgs ma) {
   };
   int64_t dq2 = 0;
   int dot = 0;  // (inner product with dot_out)
-  if (adaptive && T == 1) {
+  if (adaptive && a.dq2_in) {
+    if (p >= 0) dq2 = a.dq2_in[(size_t)q * a.npmax + r];  // the same on the T threads of the pair
+  } else if (adaptive && T == 1) {
     // a thread per pair: the rows are read by sixteen lanes per pair, sixteen
     // pairs of the workgroup at a time (coalesced 128-byte segments), and the
     // norms handed over through LDS; the thread of a pair slot is its index
@@ -748,7 +751,7 @@ __global__ __launch_bounds__(256) void k_pairs(PairArgs a, ModelArgs ma) {
     dq2 = dq2_part(q, p, t, T, dot);
   }
   // the T threads of a pair are adjacent lanes of one wave (T <= 64)
-  if (T > 1)
+  if (T > 1 && !a.dq2_in)
     for (int o = 1; o < T; o <<= 1) {
       dq2 += __shfl_xor(dq2, o);
       dot += __shfl_xor(dot, o);
@@ -1560,6 +1563,162 @@ __global__ void k_ipq(BaseArgs b) {
   }
 }
 
+// ------------------------------------------------------------------ pair bases, L2
+// Lower bound of every (query, probed list) pair's estimates on L2, and its
+// d' for the predictor.  Integer policies: the exact base, sum over the
+// subspaces of min_j T[m][j] with T = |ri_m|^2 + (|cbi|^2 - 2 ri_m . cbi).
+//
+// A v_mfma_f32_32x32x16_bf16 takes 32 codewords as its rows and 32 pairs as
+// its columns for one subspace: K holds the 8 dims (lanes 0-31 of either
+// operand) and the base-256 digits of |cbi|^2 (lanes 32-63; the pair side
+// holds their powers and an offset that keeps every sum positive, so that
+// float bit patterns order as integers and two results take one v_min3).  A
+// lane then holds 16 codewords of ONE pair: the minimum over the 256
+// codewords needs one cross-lane step per subspace, and the pair operand is
+// 16 bytes of the residual row as it sits in LDS (-2 ri in BF16, exact).
+// Every product and sum is an integer below 2^24: exact in any order.
+//
+// kBaseNT threads, NPT tiles of 32 pairs; the subspaces go in chunks of
+// kBaseCM, whose residuals the workgroup puts on the grid, then each wave
+// takes subspaces of the chunk with its 8 codeword fragments (32 registers)
+// kept over all pair tiles.  Bound by the matrix unit and the VALU minima,
+// 32 clocks each per 1024 entries (17 us at 10000 x 32 pairs, d 128, M 16),
+// and the residual rows read before them: 76 us measured, see launch_base_l2.
+// 128 registers: two workgroups per CU, one on its rows while the other
+// multiplies (161 registers, one workgroup: 104 us).
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+constexpr int kBaseCM = 16;   // subspaces per chunk
+constexpr int kBaseNT = 512;  // threads
+
+struct BaseL2Args {
+  const float* Q;
+  const float* C;
+  const u32x4* bsw;      // MFMA B fragments of the grid codebook (k_prep_bsw)
+  const int32_t* probes;
+  int64_t* pbase;        // [nq][npmax]
+  int64_t* dq2;          // [nq][npmax] squared norm of the grid residual
+  int nq, d, M, dsub, npmax, grid_e, grid_kind;
+};
+
+constexpr int base_l2_row() { return kBaseCM * 16 + 16; }  // bytes of a residual row (padded: distinct banks)
+inline size_t base_l2_lds(int npt) { return (size_t)npt * 32 * (base_l2_row() + 8 + 8 + 4 + 4); }
+
+template <int NPT>
+__global__ __launch_bounds__(kBaseNT, 4) void k_base_l2(BaseL2Args b) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  constexpr int G = NPT * 32, ROW = base_l2_row(), NW = kBaseNT / 64;
+  unsigned long long* smin = reinterpret_cast<unsigned long long*>(lds + G * ROW);  // [G] sum of the minima
+  int64_t* srr = reinterpret_cast<int64_t*>(smin + G);                              // [G] sum of |ri|^2
+  int32_t* sp = reinterpret_cast<int32_t*>(srr + G);                                // [G] list of the pair, or -1
+  int32_t* sq = sp + G;                                                             // [G] query of the pair
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = tid & 15, grp = tid >> 4;
+  const size_t n = (size_t)b.nq * b.npmax, i0 = (size_t)blockIdx.x * G;
+  for (int g = tid; g < G; g += kBaseNT) {
+    const size_t i = i0 + g;
+    sp[g] = i < n ? b.probes[i] : -1;
+    sq[g] = i < n ? (int)(i / b.npmax) : 0;
+    smin[g] = 0;
+    srr[g] = 0;
+  }
+  const int ds = b.dsub;
+  if (ds != 8 && ds != 4 && ds != 2) {
+    // rows of other widths are written element by element: the padding stays zero
+    for (int i = tid; i < G * ROW / 16; i += kBaseNT) reinterpret_cast<u32x4*>(lds)[i] = (u32x4){0u, 0u, 0u, 0u};
+  }
+  int64_t sum[NPT];
+#pragma unroll
+  for (int t = 0; t < NPT; ++t) sum[t] = 0;
+  // pair side of the |cbi|^2 digits and the offset 64 * 65536 = 2^22 (the
+  // codeword side holds 65536 there), above any 2 |ri . cbi| (at most 8 * 2 *
+  // 448^2)
+  const u32x4 aug = {0x43804780u, 0x42803F80u, 0u, 0u};  // BF16 65536, 256 | 1, 64 | 0
+  constexpr int kOff = 1 << 22;
+  for (int m0 = 0; m0 < b.M; m0 += kBaseCM) {
+    const int cm = b.M - m0 < kBaseCM ? b.M - m0 : kBaseCM;
+    const int cd4 = (cm * ds) >> 2, o4 = (m0 * ds) >> 2;  // M and the chunk are multiples of 4
+    __syncthreads();  // the last chunk's rows are read (first chunk: the lists are in)
+    // residuals onto the grid: sixteen lanes per pair, two 16-byte reads each
+#pragma unroll(NPT < 4 ? NPT : 4)
+    for (int u = 0; u < G / (kBaseNT / 16) + (G < kBaseNT / 16); ++u) {
+      const int g = grp + u * (kBaseNT / 16);
+      if (g >= G) break;
+      const int p = sp[g] < 0 ? 0 : sp[g];  // (absent pairs: any row, never written out)
+      const float4* qr = reinterpret_cast<const float4*>(b.Q + (size_t)sq[g] * b.d) + o4;
+      const float4* cr = reinterpret_cast<const float4*>(b.C + (size_t)p * b.d) + o4;
+      int s2 = 0;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int t4 = l16 + 16 * h;
+        if (t4 >= cd4) break;
+        const float4 x = qr[t4], c = cr[t4];
+        const int v0 = grid_val(x.x - c.x, b.grid_e, b.grid_kind), v1 = grid_val(x.y - c.y, b.grid_e, b.grid_kind);
+        const int v2 = grid_val(x.z - c.z, b.grid_e, b.grid_kind), v3 = grid_val(x.w - c.w, b.grid_e, b.grid_kind);
+        s2 += v0 * v0 + v1 * v1 + v2 * v2 + v3 * v3;
+        const uint32_t b0 = bf16_bits((float)(-2 * v0)), b1 = bf16_bits((float)(-2 * v1));
+        const uint32_t b2 = bf16_bits((float)(-2 * v2)), b3 = bf16_bits((float)(-2 * v3));
+        char* row = lds + g * ROW;
+        if (ds == 8) {
+          *reinterpret_cast<u32x2*>(row + t4 * 8) = (u32x2){b0 | (b1 << 16), b2 | (b3 << 16)};
+        } else if (ds == 4) {
+          *reinterpret_cast<u32x4*>(row + t4 * 16) = (u32x4){b0 | (b1 << 16), b2 | (b3 << 16), 0u, 0u};
+        } else if (ds == 2) {
+          *reinterpret_cast<u32x4*>(row + t4 * 32) = (u32x4){b0 | (b1 << 16), 0u, 0u, 0u};
+          *reinterpret_cast<u32x4*>(row + t4 * 32 + 16) = (u32x4){b2 | (b3 << 16), 0u, 0u, 0u};
+        } else {
+          const uint32_t bv[4] = {b0, b1, b2, b3};
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const int t = 4 * t4 + k;
+            *reinterpret_cast<uint16_t*>(row + (t / ds) * 16 + (t % ds) * 2) = (uint16_t)bv[k];
+          }
+        }
+      }
+#pragma unroll
+      for (int o = 8; o > 0; o >>= 1) s2 += __shfl_xor(s2, o, 16);
+      if (l16 == 0) srr[g] += s2;
+    }
+    __syncthreads();
+    for (int mi = wave; mi < cm; mi += NW) {
+      const int m = m0 + mi;
+      // codeword fragments of the subspace: 32 codewords per tile, dims in
+      // lanes 0-31, digits in lanes 32-63
+      const u32x4* src = b.bsw + (size_t)(m >> 1) * 1024 + (2 * (m & 1) + (lane >> 5)) * 16 + (lane & 15) +
+                         ((lane >> 4) & 1) * 64;
+      u32x4 cw[8];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) cw[t] = src[t * 128];
+#pragma unroll
+      for (int pt = 0; pt < NPT; ++pt) {
+        u32x4 pr = aug;
+        if (lane < 32) pr = *reinterpret_cast<const u32x4*>(lds + (pt * 32 + lane) * ROW + mi * 16);
+        int run = 0x7FFFFFFF;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+          const f32x16 z = {};
+          const f32x16 a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, cw[t]),
+                                                                   __builtin_bit_cast(bf16x8, pr), z, 0, 0, 0);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int v = __float_as_int(a[r]);
+            run = v < run ? v : run;
+          }
+        }
+        const int o = __shfl_xor(run, 32);
+        sum[pt] += (int)__int_as_float(o < run ? o : run) - kOff;
+      }
+    }
+  }
+#pragma unroll
+  for (int pt = 0; pt < NPT; ++pt)
+    if (lane < 32) atomicAdd(&smin[pt * 32 + lane], (unsigned long long)sum[pt]);
+  __syncthreads();
+  for (int g = tid; g < G; g += kBaseNT)
+    if (sp[g] >= 0) {
+      b.pbase[i0 + g] = (int64_t)smin[g] + srr[g];
+      b.dq2[i0 + g] = srr[g];
+    }
+}
+
 // ------------------------------------------------------------------ host launchers
 template <typename K>
 static void* kaddr(K k) { return reinterpret_cast<void*>(k); }
@@ -1666,6 +1825,26 @@ hipError_t launch_residual(const float* X, const int32_t* a, const float* C, int
   return hipGetLastError();
 }
 
+// as many pairs per workgroup (128 at most: they share the codeword
+// fragments, M * 8 KB from L2) as leave three workgroups for two CUs.  With
+// 32 / 64 / 128 / 256 pairs: 110 / 87 / 76 / 76 us at 10000 x 32 pairs,
+// d 128, M 16; 165 / 143 / 136 / 182 us at 1000 x 64, d 960, M 120 (500
+// workgroups of 128); 211 / 166 / 145 / 144 us at 4096 x 8..128, d 96, M 24.
+// (The 16x16x32 tiles before, with the residual's operand converted for every
+// tile and a cross-lane reduction per 16 codewords: 231, 640 and 480 us, and
+// the predictor read the same rows again: 41 -> 19, 96 -> 12, 194 -> 168 us.)
+static hipError_t launch_base_l2(const BaseL2Args& b, hipStream_t st) {
+  const size_t n = (size_t)b.nq * b.npmax;
+  int npt = 4;
+  while (npt > 1 && n < (size_t)npt * 32 * 384) npt >>= 1;
+  auto fn = npt == 4 ? k_base_l2<4> : (npt == 2 ? k_base_l2<2> : k_base_l2<1>);
+  const size_t lds = base_l2_lds(npt);
+  const hipError_t e = hipFuncSetAttribute(kaddr(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(fn, dim3((unsigned)((n + npt * 32 - 1) / (npt * 32))), dim3(kBaseNT), lds, st, b);
+  return hipGetLastError();
+}
+
 hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* queries_in, const SearchDims& sd,
                          const ModelArgs& ma, const ModelArgs& clma, int64_t* out_ids, float* out_dist,
                          int64_t* out_qdist,
@@ -1769,6 +1948,34 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
     hipLaunchKernelGGL(k_qgrid, dim3((unsigned)std::min<size_t>((nel + 255) / 256, 65536)), dim3(256), 0, st, queries,
                        ws.qi16, nel, sd.grid_e, sd.grid_kind);
   }
+  const int dt = dt_of(sd.lut_dtype);
+  // exact bases of the pairs (integer policies): the full scan's queue is
+  // built after the phase-1 bound and leaves out the pairs whose base exceeds
+  // it.  (The FP32 policy tests its bound inside the scan, after its LUT.)
+  const bool early = (!fp32 || ipm) && !sd.noskip;
+  // L2, exact LUT builds: the base kernel reads every pair's rows and leaves
+  // d' for the predictor, so it runs first (in the rank array, which the
+  // queue fills later); the caller's stage times are put in order again
+  const bool base_first = sd.metric == AMP_L2 && !fp32 && dt != DT_F8 && early;
+  if (base_first) {
+    BaseL2Args bl;
+    bl.Q = queries;
+    bl.C = dv.centroids;
+    bl.bsw = reinterpret_cast<const u32x4*>(dv.bsw);
+    bl.probes = ws.probes;
+    bl.pbase = ws.pbase;
+    bl.dq2 = reinterpret_cast<int64_t*>(ws.rank);
+    bl.nq = sd.nq;
+    bl.d = sd.d;
+    bl.M = sd.M;
+    bl.dsub = sd.dsub;
+    bl.npmax = sd.npmax;
+    bl.grid_e = sd.grid_e;
+    bl.grid_kind = sd.grid_kind;
+    const hipError_t e = launch_base_l2(bl, st);
+    if (e != hipSuccess) return e;
+    mark(3);
+  }
   // PPM
   PairArgs pa;
   pa.Q = queries;
@@ -1776,6 +1983,7 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
   pa.qi16 = (ipm && !fp32) ? ws.qi16 : nullptr;
   pa.ci16 = dv.ci16;
   const bool pdot = ipm && !fp32 && sd.policy == AMP_POLICY_ADAPTIVE;
+  pa.dq2_in = base_first ? reinterpret_cast<const int64_t*>(ws.rank) : nullptr;
   pa.dot_out = pdot ? ws.pbase : nullptr;
   pa.ipmask = pdot ? ws.ipmask : nullptr;
   pa.probes = ws.probes;
@@ -1803,14 +2011,9 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
     ++pa.lg_T;
   const int qpb = 256 >> (pa.lg_npp + pa.lg_T);
   hipLaunchKernelGGL(k_pairs, dim3((sd.nq + qpb - 1) / qpb), dim3(256), 0, st, pa, ma);
-  mark(3);
-  // exact bases of the pairs (integer policies): the full scan's queue is
-  // built after the phase-1 bound and leaves out the pairs whose base exceeds
-  // it.  (The FP32 policy tests its bound inside the scan, after its LUT.)
-  const bool early = (!fp32 || ipm) && !sd.noskip;
-  const int dt = dt_of(sd.lut_dtype);
+  mark(base_first ? 4 : 3);
   hipError_t err = hipSuccess;
-  {
+  if (!base_first) {
     BaseArgs ba;
     ba.Q = queries;
     ba.C = dv.centroids;
@@ -1862,19 +2065,20 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
       const size_t nq8 = (size_t)sd.nq * sd.M * kKsub / 8;
       hipLaunchKernelGGL(k_ipq, dim3((unsigned)std::min<size_t>((nq8 + 255) / 256, 1 << 20)), dim3(256), 0, st, ba);
     } else if (early) {
-      // L2 / L1: every pair's LUT minima, as many pairs per workgroup as
-      // fit 64 KB of residual rows (128 at most): they share the B fragments
+      // L1, or the FP8 build: every pair's LUT minima, as many pairs per
+      // workgroup as fit 64 KB of residual rows (128 at most): they share the
+      // B fragments
       int G = 128;
       while (G > 8 && (size_t)G * ri_stride(sd.d) * 2 > 65536) G >>= 1;
       ba.G = G;
       const size_t blds = base_lds_layout(G, sd.M, sd.d).total;
-      auto fn = dt == DT_F16 ? k_base<DT_F16> : (dt == DT_F8 ? k_base<DT_F8> : k_base<DT_BF16>);
+      auto fn = k_base<DT_F8>;  // (L1 has no MFMA dtype)
       if ((err = hipFuncSetAttribute(kaddr(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)blds)) != hipSuccess)
         return err;
       hipLaunchKernelGGL(fn, dim3((unsigned)((npairs + G - 1) / G)), dim3(kThreads), blds, st, ba);
     }
+    mark(4);
   }
-  mark(4);
   // queue
   QueueArgs qa;
   qa.probes = ws.probes;

@@ -1626,7 +1626,8 @@ __device__ __forceinline__ void base_frags(const BaseArgs& b, int mp, int lane, 
   }
 }
 
-// L2 / L1: b.G consecutive pair slots per workgroup (any queries, any
+// L1 and the FP8 build (L2 with an exact build: k_base_l2): b.G consecutive
+// pair slots per workgroup (any queries, any
 // lists; empty slots have zero rows and write nothing).  Every m-pair's B
 // fragments, loaded once per workgroup and wave, serve all G pairs.
 template <int DT>
