@@ -68,6 +68,8 @@ struct DeviceIndex {
   uint4* bsw = nullptr;        // [M/2][16][64] MFMA B fragments (8 bf16 each)
   uint4* bsw16 = nullptr;      // [M/2][16][64] FP16 dims fragments
   uint2* bsw8 = nullptr;       // [M/2][16][64] FP8 (e4m3) dims fragments
+  uint4* bswf = nullptr;       // [M][8][2][64] split-BF16 fragments of the FP32 codebook, then one float
+                               // (L2: FP32 policy's pair bounds, see k_prep_bswf)
   int16_t* cbi16 = nullptr;    // [M][256][8] grid codebook (L1 LUT build)
   int16_t* ci16 = nullptr;     // [nlist][d] grid centroids (inner product: qi.ci, d')
   int32_t* lorder = nullptr;   // [nlist] lists by decreasing size (ties: id)

@@ -46,7 +46,7 @@ static amp_status dalloc(T** p, size_t n, std::vector<void*>* track = nullptr) {
 }
 
 static void free_device_index(DeviceIndex& d) {
-  void* ptrs[] = {d.centroids, d.cnorm, d.codebook, d.bsw, d.bsw16, d.bsw8, d.cbi16, d.ci16, d.lorder, d.lpos, d.codes, d.ids,
+  void* ptrs[] = {d.centroids, d.cnorm, d.codebook, d.bsw, d.bsw16, d.bsw8, d.bswf, d.cbi16, d.ci16, d.lorder, d.lpos, d.codes, d.ids,
                   d.offsets, d.radq, d.model.sv, d.model.beta, d.model.table, d.clc, d.clasg, d.clz, d.clr,
                   d.cln, d.clmodel.sv, d.clmodel.beta, d.clmodel.table, d.cltab};
   for (void* p : ptrs)
@@ -304,7 +304,7 @@ static amp_status to_device_locked(amp_index* ix, int device) {
   if ((s = dalloc(&d.centroids, nl * dd)) || (s = dalloc(&d.cnorm, nl)) ||
       (s = dalloc(&d.codebook, M * kKsub * ix->dsub)) || (s = dalloc(&d.bsw, (M / 2) * 16 * 64)) ||
       (s = dalloc(&d.bsw16, (M / 2) * 16 * 64)) || (s = dalloc(&d.bsw8, (M / 2) * 16 * 64)) || (s = dalloc(&d.cbi16, M * kKsub * 8)) || (s = dalloc(&d.ci16, nl * dd)) ||
-      (s = dalloc(&d.lorder, nl)) || (s = dalloc(&d.lpos, nl)) ||
+      (ix->metric == AMP_L2 && (s = dalloc(&d.bswf, M * 1024 + 1))) || (s = dalloc(&d.lorder, nl)) || (s = dalloc(&d.lpos, nl)) ||
       (s = dalloc(&d.codes, std::max<size_t>(1, n * M))) || (s = dalloc(&d.ids, std::max<size_t>(1, n))) ||
       (s = dalloc(&d.offsets, nl + 1)) || (s = dalloc(&d.radq, nl))) {
     free_device_index(d);

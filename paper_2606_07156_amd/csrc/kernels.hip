@@ -1393,6 +1393,62 @@ __global__ void k_prep_bsw(const float* __restrict__ cb, int M, int dsub, int gr
   bsw8[idx] = (u32x2){f8[0], f8[1]};
 }
 
+// L2, FP32 policy: fragments of the FP32 codebook for the pair bounds
+// (k_base_l2f).  For subspace m, tile t of 32 codewords and lane l (codeword
+// j = 32 t + l % 32): fragment 0 holds the BF16 high parts of the codeword's
+// dims (lanes 0-31) and the BF16 low parts (the rest rounded, lanes 32-63);
+// fragment 1 the high parts again, |c|^2 in three BF16 pieces and three ones
+// (for the pieces of |r|^2).  The word
+// after the last fragment is the sum over the subspaces of the largest |c|^2.
+__device__ __forceinline__ uint32_t bf16_rn(float v, float& rest) {
+  const __bf16 h = (__bf16)v;
+  rest = v - (float)h;
+  return (uint32_t)__builtin_bit_cast(uint16_t, h);
+}
+__global__ void k_prep_bswf(const float* __restrict__ cb, int M, int dsub, u32x4* __restrict__ bswf) {
+  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx >= M * 8 * 64) return;
+  const int lane = idx & 63, t = (idx >> 6) & 7, m = idx >> 9;
+  const float* c = cb + ((size_t)m * kKsub + t * 32 + (lane & 31)) * dsub;
+  uint32_t hi[8], lo[8];
+  float cc = 0.f;
+  for (int i = 0; i < 8; ++i) {
+    const float v = i < dsub ? c[i] : 0.f;
+    float r;
+    hi[i] = bf16_rn(v, r);
+    lo[i] = bf16_rn(r, r);
+    cc = fmaf(v, v, cc);
+  }
+  const u32x4 h = {hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16), hi[4] | (hi[5] << 16), hi[6] | (hi[7] << 16)};
+  const u32x4 l = {lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16), lo[4] | (lo[5] << 16), lo[6] | (lo[7] << 16)};
+  float r;
+  const uint32_t c0 = bf16_rn(cc, r), c1 = bf16_rn(r, r), c2 = bf16_rn(r, r);
+  u32x4* o = bswf + ((size_t)(m * 8 + t) * 2) * 64 + lane;
+  o[0] = lane < 32 ? h : l;
+  o[64] = lane < 32 ? h : (u32x4){c0 | (c1 << 16), c2 | 0x3F800000u, 0x3F803F80u, 0u};
+}
+__global__ __launch_bounds__(256) void k_prep_cbsum(const float* __restrict__ cb, int M, int dsub, float* out) {
+  __shared__ float s_w[4];
+  float sum = 0.f;
+  for (int m = 0; m < M; ++m) {
+    const float* c = cb + ((size_t)m * kKsub + threadIdx.x) * dsub;
+    float cc = 0.f;
+    for (int i = 0; i < dsub; ++i) cc = fmaf(c[i], c[i], cc);
+    // (a NaN must survive the maximum: it disables the bounds)
+    for (int o = 32; o > 0; o >>= 1) {
+      const float v = __shfl_xor(cc, o);
+      cc = v > cc || v != v ? v : cc;
+    }
+    if ((threadIdx.x & 63) == 0) s_w[threadIdx.x >> 6] = cc;
+    __syncthreads();
+    float mx = s_w[0];
+    for (int w = 1; w < 4; ++w) mx = s_w[w] > mx || s_w[w] != s_w[w] ? s_w[w] : mx;
+    sum += mx;
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) *out = sum;
+}
+
 // ------------------------------------------------------------------ inner-product tables
 // queries on the operand grid (inner product)
 __global__ void k_qgrid(const float* __restrict__ Q, int16_t* __restrict__ qi, size_t n, int grid_e, int grid_kind) {
@@ -1719,6 +1775,191 @@ __global__ __launch_bounds__(kBaseNT, 4) void k_base_l2(BaseL2Args b) {
     }
 }
 
+// FP32 policy: a lower bound of every pair's in-order FP32 sums, as the key
+// the queue compares with the phase-1 bound.  The FP32 LUT of a pair takes 8
+// dependent FMAs per entry on the VALU, and most pairs need it only to be
+// found dead (26 of 27 at 4999 x 32 pairs, d 128, M 16: the full scan of that
+// batch took 2546 us and takes 190 without them; these bounds take 49).  Here
+// |r|^2 + |c|^2 - 2 r . c of a 32 x 32 tile comes from two BF16 MFMAs of the
+// operands split into high and low parts (lo . lo left out), with |c|^2 and
+// |r|^2 in three pieces each; bound by the matrix unit, 64 clocks per 1024
+// entries (9 us at that size), and by the residual rows read and split.
+// Errors, in units of |r_m|^2 + max_j |c_mj|^2 of a subspace: the split
+// 3 * 2^-18 (2 |r| |c| <= |r|^2 + |c|^2), |r|^2 from the rounded parts 2^-17,
+// accumulation 20 terms * 2^-23 * 2, the scan's own entry 24 * 2^-24 and its
+// sum M * 2^-23: together below 2^-15 + M * 2^-23, and twice that is taken
+// off the sum.  A minimum by integer order takes a negative value nearest to
+// zero, off by at most the same error.  A sum or slack that is not finite (or
+// near overflow) gives key 0: the scan decides.  The scan still tests the
+// exact bound of the pairs that pass.
+struct BaseL2FArgs {
+  const float* Q;
+  const float* C;
+  const u32x4* bswf;
+  const int32_t* probes;
+  int64_t* pbase;        // [nq][npmax] keys
+  int nq, d, M, dsub, npmax;
+};
+
+constexpr int base_l2f_row() { return kBaseCM * 32 + 16; }  // high and low halves side by side, padded
+constexpr int kBaseRr = kBaseCM + 1;                        // |r_m|^2 row, padded
+inline size_t base_l2f_lds(int npt) {
+  return (size_t)npt * 32 * (base_l2f_row() + kBaseRr * 4 + 4 * (kBaseNT / 64 + 3));
+}
+
+template <int NPT>
+__global__ __launch_bounds__(kBaseNT, 4) void k_base_l2f(BaseL2FArgs b) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  constexpr int G = NPT * 32, ROW = base_l2f_row(), NW = kBaseNT / 64;
+  float* rr = reinterpret_cast<float*>(lds + G * ROW);  // [G][kBaseRr]
+  float* part = rr + G * kBaseRr;                       // [NW][G] sums of the waves
+  float* srr = part + NW * G;                           // [G] sum of |r|^2
+  int32_t* sp = reinterpret_cast<int32_t*>(srr + G);
+  int32_t* sq = sp + G;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = tid & 15, grp = tid >> 4;
+  const size_t n = (size_t)b.nq * b.npmax, i0 = (size_t)blockIdx.x * G;
+  for (int g = tid; g < G; g += kBaseNT) {
+    const size_t i = i0 + g;
+    sp[g] = i < n ? b.probes[i] : -1;
+    sq[g] = i < n ? (int)(i / b.npmax) : 0;
+    srr[g] = 0.f;
+  }
+  const int ds = b.dsub;
+  if (ds != 8 && ds != 4)  // element-wise rows: the padding stays zero
+    for (int i = tid; i < G * ROW / 16; i += kBaseNT) reinterpret_cast<u32x4*>(lds)[i] = (u32x4){0u, 0u, 0u, 0u};
+  float sum[NPT];
+#pragma unroll
+  for (int t = 0; t < NPT; ++t) sum[t] = 0.f;
+  for (int m0 = 0; m0 < b.M; m0 += kBaseCM) {
+    const int cm = b.M - m0 < kBaseCM ? b.M - m0 : kBaseCM;
+    const int cd4 = (cm * ds) >> 2, o4 = (m0 * ds) >> 2;
+    __syncthreads();
+#pragma unroll(NPT < 2 ? NPT : 2)
+    for (int u = 0; u < NPT; ++u) {
+      const int g = grp + u * (kBaseNT / 16);
+      const int p = sp[g] < 0 ? 0 : sp[g];
+      const float4* qr = reinterpret_cast<const float4*>(b.Q + (size_t)sq[g] * b.d) + o4;
+      const float4* cr = reinterpret_cast<const float4*>(b.C + (size_t)p * b.d) + o4;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int t4 = l16 + 16 * h;
+        if (t4 >= cd4) break;
+        const float4 x = qr[t4], c = cr[t4];
+        const float v[4] = {-2.f * (x.x - c.x), -2.f * (x.y - c.y), -2.f * (x.z - c.z), -2.f * (x.w - c.w)};
+        uint32_t hi[4], lo[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          float r;
+          hi[k] = bf16_rn(v[k], r);
+          lo[k] = bf16_rn(r, r);
+        }
+        char* row = lds + g * ROW;
+        if (ds == 8) {
+          char* w = row + (t4 >> 1) * 32 + (t4 & 1) * 8;
+          *reinterpret_cast<u32x2*>(w) = (u32x2){hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16)};
+          *reinterpret_cast<u32x2*>(w + 16) = (u32x2){lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16)};
+        } else if (ds == 4) {
+          char* w = row + t4 * 32;
+          *reinterpret_cast<u32x4*>(w) = (u32x4){hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16), 0u, 0u};
+          *reinterpret_cast<u32x4*>(w + 16) = (u32x4){lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16), 0u, 0u};
+        } else {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const int t = 4 * t4 + k;
+            char* w = row + (t / ds) * 32 + (t % ds) * 2;
+            *reinterpret_cast<uint16_t*>(w) = (uint16_t)hi[k];
+            *reinterpret_cast<uint16_t*>(w + 16) = (uint16_t)lo[k];
+          }
+        }
+      }
+    }
+    __syncthreads();
+    // |r_m|^2 from the split parts
+    for (int e = tid; e < G * cm; e += kBaseNT) {
+      const int g = e / cm, mi = e - g * cm;
+      const u32x4 h = *reinterpret_cast<const u32x4*>(lds + g * ROW + mi * 32);
+      const u32x4 l = *reinterpret_cast<const u32x4*>(lds + g * ROW + mi * 32 + 16);
+      float s = 0.f;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float a = __uint_as_float(h[k] << 16) + __uint_as_float(l[k] << 16);
+        const float c = __uint_as_float(h[k] & 0xFFFF0000u) + __uint_as_float(l[k] & 0xFFFF0000u);
+        s = fmaf(a, a, s);
+        s = fmaf(c, c, s);
+      }
+      rr[g * kBaseRr + mi] = 0.25f * s;  // (the parts are those of -2 r)
+    }
+    __syncthreads();
+    if (tid < G) {
+      float s = srr[tid];
+      for (int mi = 0; mi < cm; ++mi) s += rr[tid * kBaseRr + mi];
+      srr[tid] = s;
+    }
+    for (int mi = wave; mi < cm; mi += NW) {
+      int run[NPT];
+#pragma unroll
+      for (int t = 0; t < NPT; ++t) run[t] = 0x7FFFFFFF;
+      // four codeword tiles at a time: their fragments stay in 32 registers
+#pragma unroll
+      for (int th = 0; th < 2; ++th) {
+        const u32x4* src = b.bswf + (size_t)((m0 + mi) * 8 + th * 4) * 128 + lane;
+        u32x4 c0[4], c1[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          c0[t] = src[t * 128];
+          c1[t] = src[t * 128 + 64];
+        }
+#pragma unroll
+        for (int pt = 0; pt < NPT; ++pt) {
+          const int g = pt * 32 + (lane & 31);
+          const u32x4 p0 = *reinterpret_cast<const u32x4*>(lds + g * ROW + mi * 32);
+          float r = rr[g * kBaseRr + mi];
+          const uint32_t r0 = bf16_rn(r, r), r1 = bf16_rn(r, r), r2 = bf16_rn(r, r);
+          u32x4 p1 = {0x3F803F80u, 0x00003F80u | (r0 << 16), r1 | (r2 << 16), 0u};  // for the pieces of |c|^2: ones
+          if (lane < 32) p1 = *reinterpret_cast<const u32x4*>(lds + g * ROW + mi * 32 + 16);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            f32x16 a = {};
+            a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, c0[t]),
+                                                        __builtin_bit_cast(bf16x8, p0), a, 0, 0, 0);
+            a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, c1[t]),
+                                                        __builtin_bit_cast(bf16x8, p1), a, 0, 0, 0);
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+              const int v = __float_as_int(a[k]);
+              run[pt] = v < run[pt] ? v : run[pt];
+            }
+            // (an opaque step: reassociated into one tree, the minima would
+            // keep every tile's accumulators alive)
+            asm volatile("" : "+v"(run[pt]));
+          }
+        }
+      }
+#pragma unroll
+      for (int pt = 0; pt < NPT; ++pt) {
+        const int o = __shfl_xor(run[pt], 32);
+        sum[pt] += __int_as_float(o < run[pt] ? o : run[pt]);
+      }
+    }
+  }
+#pragma unroll
+  for (int pt = 0; pt < NPT; ++pt)
+    if (lane < 32) part[wave * G + pt * 32 + lane] = sum[pt];
+  __syncthreads();
+  const float cbsum = *reinterpret_cast<const float*>(b.bswf + (size_t)b.M * 1024);
+  for (int g = tid; g < G; g += kBaseNT)
+    if (sp[g] >= 0) {
+      float s = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) s += part[w * G + g];
+      const float mag = srr[g] + cbsum;
+      // (the absolute term covers squares that underflow)
+      const float lb = s - (mag * (0x1p-14f + (float)b.M * 0x1p-22f) + (float)b.M * 1e-30f);
+      const bool ok = mag < 1e37f && lb > -3e38f && lb < 3e38f;  // false for NaN
+      b.pbase[i0 + g] = ok ? (int64_t)fkey(lb) : 0;
+    }
+}
+
 // ------------------------------------------------------------------ host launchers
 template <typename K>
 static void* kaddr(K k) { return reinterpret_cast<void*>(k); }
@@ -1736,6 +1977,12 @@ hipError_t launch_prep_index(const amp_index* ix, hipStream_t st) {
   hipLaunchKernelGGL(k_prep_bsw, dim3((total + 255) / 256), dim3(256), 0, st, dv.codebook, ix->M, ix->dsub,
                      ix->grid_e, ix->grid_kind, reinterpret_cast<u32x4*>(dv.bsw),
                      reinterpret_cast<u32x4*>(dv.bsw16), reinterpret_cast<u32x2*>(dv.bsw8));
+  if (ix->metric == AMP_L2) {
+    u32x4* f = reinterpret_cast<u32x4*>(dv.bswf);
+    hipLaunchKernelGGL(k_prep_bswf, dim3((ix->M * 512 + 255) / 256), dim3(256), 0, st, dv.codebook, ix->M, ix->dsub, f);
+    hipLaunchKernelGGL(k_prep_cbsum, dim3(1), dim3(256), 0, st, dv.codebook, ix->M, ix->dsub,
+                       reinterpret_cast<float*>(f + (size_t)ix->M * 1024));
+  }
   return hipGetLastError();
 }
 
@@ -1833,12 +2080,28 @@ hipError_t launch_residual(const float* X, const int32_t* a, const float* C, int
 // (The 16x16x32 tiles before, with the residual's operand converted for every
 // tile and a cross-lane reduction per 16 codewords: 231, 640 and 480 us, and
 // the predictor read the same rows again: 41 -> 19, 96 -> 12, 194 -> 168 us.)
-static hipError_t launch_base_l2(const BaseL2Args& b, hipStream_t st) {
-  const size_t n = (size_t)b.nq * b.npmax;
+static int base_l2_npt(size_t n) {
   int npt = 4;
   while (npt > 1 && n < (size_t)npt * 32 * 384) npt >>= 1;
+  return npt;
+}
+
+static hipError_t launch_base_l2(const BaseL2Args& b, hipStream_t st) {
+  const size_t n = (size_t)b.nq * b.npmax;
+  const int npt = base_l2_npt(n);
   auto fn = npt == 4 ? k_base_l2<4> : (npt == 2 ? k_base_l2<2> : k_base_l2<1>);
   const size_t lds = base_l2_lds(npt);
+  const hipError_t e = hipFuncSetAttribute(kaddr(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(fn, dim3((unsigned)((n + npt * 32 - 1) / (npt * 32))), dim3(kBaseNT), lds, st, b);
+  return hipGetLastError();
+}
+
+static hipError_t launch_base_l2f(const BaseL2FArgs& b, hipStream_t st) {
+  const size_t n = (size_t)b.nq * b.npmax;
+  const int npt = base_l2_npt(n);
+  auto fn = npt == 4 ? k_base_l2f<4> : (npt == 2 ? k_base_l2f<2> : k_base_l2f<1>);
+  const size_t lds = base_l2f_lds(npt);
   const hipError_t e = hipFuncSetAttribute(kaddr(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(fn, dim3((unsigned)((n + npt * 32 - 1) / (npt * 32))), dim3(kBaseNT), lds, st, b);
@@ -1949,10 +2212,11 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
                        ws.qi16, nel, sd.grid_e, sd.grid_kind);
   }
   const int dt = dt_of(sd.lut_dtype);
-  // exact bases of the pairs (integer policies): the full scan's queue is
-  // built after the phase-1 bound and leaves out the pairs whose base exceeds
-  // it.  (The FP32 policy tests its bound inside the scan, after its LUT.)
-  const bool early = (!fp32 || ipm) && !sd.noskip;
+  // lower bounds of the pairs' estimates (integer policies: the exact bases):
+  // the full scan's queue is built after the phase-1 bound and leaves out the
+  // pairs whose bound exceeds it.  (The FP32 policy under L1 tests its bound
+  // inside the scan, after its LUT.)
+  const bool early = (!fp32 || sd.metric != AMP_L1) && !sd.noskip;
   // L2, exact LUT builds: the base kernel reads every pair's rows and leaves
   // d' for the predictor, so it runs first (in the rank array, which the
   // queue fills later); the caller's stage times are put in order again
@@ -2043,7 +2307,20 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
     ba.grid_kind = sd.grid_kind;
     ba.metric = sd.metric;
     ba.gran = sd.gran;
-    if (ipm && fp32) {
+    if (fp32 && sd.metric == AMP_L2 && early) {
+      BaseL2FArgs bf;
+      bf.Q = queries;
+      bf.C = dv.centroids;
+      bf.bswf = reinterpret_cast<const u32x4*>(dv.bswf);
+      bf.probes = ws.probes;
+      bf.pbase = ws.pbase;
+      bf.nq = sd.nq;
+      bf.d = sd.d;
+      bf.M = sd.M;
+      bf.dsub = sd.dsub;
+      bf.npmax = sd.npmax;
+      if ((err = launch_base_l2f(bf, st)) != hipSuccess) return err;
+    } else if (ipm && fp32) {
       // the queries' FP32 dot-product tables, their row maxima, the pairs'
       // FP32 lower bounds
       const size_t n = (size_t)sd.nq * sd.M * kKsub;
@@ -2064,7 +2341,7 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
       hipLaunchKernelGGL(fn, dim3((sd.nq + kTabQ - 1) / kTabQ), dim3(kThreads), tlds, st, ba);
       const size_t nq8 = (size_t)sd.nq * sd.M * kKsub / 8;
       hipLaunchKernelGGL(k_ipq, dim3((unsigned)std::min<size_t>((nq8 + 255) / 256, 1 << 20)), dim3(256), 0, st, ba);
-    } else if (early) {
+    } else if (early && !fp32) {
       // L1, or the FP8 build: every pair's LUT minima, as many pairs per
       // workgroup as fit 64 KB of residual rows (128 at most): they share the
       // B fragments

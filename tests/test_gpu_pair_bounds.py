@@ -32,11 +32,19 @@ def random_index(seed, M, dsub, nlist=40, n=6000, metric="l2", scale=3.0, grid_e
 # (pairs, nprobe): one pair, around a tile of 32, ragged tiles, and batches of
 # one, two and four tiles per workgroup (from 384 workgroups on)
 SIZES = [(1, 1), (31, 31), (33, 11), (257, 1), (24_552, 33), (24_579, 9), (49_152, 12), (66_003, 9)]
+# queries with no usable bound (a NaN, squares that overflow) and with squares
+# that underflow: the scan decides.  (It finds the pairs of an infinite query
+# dead by its own bound, which AMP_PAIR_SKIP=0 turns off: no reference here.)
+def odd_queries(Q):
+    Q[0, 0], Q[2, 1], Q[3] = np.nan, -1e30, 1e-25
+    return Q
+
+
 SHAPES = [(16, 8), (24, 4), (32, 2), (12, 1), (20, 3), (36, 6), (120, 8)]
 
 
 @pytest.mark.parametrize("M,dsub", SHAPES)
-@pytest.mark.parametrize("policy", ["adaptive", "fixed"])
+@pytest.mark.parametrize("policy", ["adaptive", "fixed", "fp32"])
 def test_dropping_pairs_by_their_bound_changes_nothing(monkeypatch, M, dsub, policy):
     idx = random_index(M * 10 + dsub, M, dsub)
     h = amp.amp_index_from_arrays(idx)
@@ -64,3 +72,16 @@ def test_dropping_pairs_by_their_bound_changes_nothing(monkeypatch, M, dsub, pol
         assert np_q.sum() - empty <= counted <= np_q.sum()
         dropped += got["work"]["dead_pairs"]
     assert dropped > 0
+
+
+@pytest.mark.parametrize("M,dsub", [(16, 8), (20, 3)])
+def test_fp32_bounds_of_odd_queries(monkeypatch, M, dsub):
+    idx = random_index(3 + M, M, dsub)
+    h = amp.amp_index_from_arrays(idx)
+    r = np.random.default_rng(M)
+    Q = odd_queries((idx["centroids"][r.integers(0, 40, 64)] + r.standard_normal((64, idx["d"]))).astype(np.float32))
+    got = amp.amp_search(h, Q, 5, 20, policy="fp32")
+    monkeypatch.setenv("AMP_PAIR_SKIP", "0")
+    want = amp.amp_search(h, Q, 5, 20, policy="fp32")
+    for f in ("ids", "dist"):
+        assert np.array_equal(got[f], want[f], equal_nan=f == "dist"), f
