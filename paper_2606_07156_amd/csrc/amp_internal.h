@@ -48,9 +48,28 @@ inline int lane_class(int M, int b, int gran = 0) {
   if (top <= 0xFFFFull) return 1;
   return 2;
 }
-// lane bits of a class: class 0 holds 4-bit entries with one width per pair
-// (width-4 pairs only), 8-bit ones with per-subspace widths
-inline int lane_bits(int cls, int gran) { return cls == 0 && gran == 0 ? 4 : 8 << cls; }
+// How a LUT word holds and the scan adds the entries of a class ("lane bits"
+// of the kernels' template arguments).  4, 8, 16, 32: entries in lanes of
+// that width (4: nibbles, two words of 8-bit sums widened every kWideChunk
+// subspaces).  kLwByte: byte entries, 16-bit sums; kLwHalf: 16-bit entries,
+// 32-bit sums: with one width per pair an entry never exceeds its own width,
+// so it is stored at that width and only the sums are wider (see scan_unit),
+// twice the pairs per LUT row read of lanes as wide as the sums (whole
+// searches with the 16- and 32-bit lanes before: 4096 queries over 10M x 96,
+// M 24: 3.52 -> 2.33 ms; 5M x 768, M 96: 2.83 -> 2.60 ms; 1000 queries, d 960,
+// M 120: 0.61 -> 0.45 ms).
+constexpr int kLwByte = 12, kLwHalf = 24;
+// subspace counts whose class 1 is byte entries: above 16 it holds 8-bit pairs
+// only (12-bit sums need more than 16 bits), up to 128 their sums leave the
+// guard bit of a 16-bit half free
+__host__ __device__ constexpr bool byte_class(int M) { return M > 16 && M <= 128; }
+__host__ __device__ constexpr int lane_bits(int cls, int gran, int M) {
+  return gran ? 8 << cls : (cls == 0 ? 4 : (cls == 2 ? kLwHalf : (byte_class(M) ? kLwByte : 16)));
+}
+// entries per LUT word
+__host__ __device__ constexpr int lane_fields(int lwb) {
+  return lwb == 0 ? 1 : (lwb == kLwByte ? 4 : (lwb == kLwHalf ? 2 : 32 / lwb));
+}
 
 // -------------------------------------------------------------- device data
 struct DeviceModel {

@@ -884,9 +884,9 @@ __device__ __forceinline__ int pair_class(int bits, int M, int gran) {
   uint64_t top = (uint64_t)M * ((1ull << bits) - 1);
   return top <= 0xFFull ? 0 : (top <= 0xFFFFull ? 1 : 2);
 }
-// pairs of a work unit: WPR LUT words of 32 / lane_bits(class) fields
-__device__ __forceinline__ int class_pairs(int cls, int wpr, bool fp32, int gran) {
-  return fp32 ? wpr : (cls == 0 && !gran ? unit_pairs(4, wpr) : wpr * (4 >> cls));
+// pairs of a work unit: the LUT words of its class's rows times their fields
+__device__ __forceinline__ int class_pairs(int cls, int wpr, bool fp32, int gran, int M) {
+  return fp32 ? wpr : unit_pairs(lane_bits(cls, gran, M), wpr);
 }
 
 // sub-counter of a pair: the pairs of a much-probed list spread over kQSub
@@ -952,7 +952,7 @@ __global__ void k_qtot(QueueArgs a, int fp32) {
   for (int u = 0; u < kQSub; ++u) cnt[(size_t)u * NB + b] = x[u];
   const int64_t n = a.offsets[p + 1] - a.offsets[p];
   const int64_t nch = (n + a.chunk[ph] - 1) / a.chunk[ph];
-  const int G = class_pairs(cls, a.wpr, fp32, a.gran);
+  const int G = class_pairs(cls, a.wpr, fp32, a.gran, a.M);
   const int pos = cls * a.nlist + a.lpos[p];
   a.pairoff[(size_t)ph * (NB + 1) + pos] = c;
   a.unitoff[(size_t)ph * (NB + 1) + pos] = ((c + G - 1) / G) * nch;
@@ -1053,7 +1053,7 @@ __global__ void k_qunits(QueueArgs a, int fp32) {
       const int b = lo, cls = b / a.nlist, p = a.lorder[b % a.nlist];
       const int64_t n = a.offsets[p + 1] - a.offsets[p];
       const int64_t nch = (n + a.chunk[ph] - 1) / a.chunk[ph];
-      const int G = class_pairs(cls, a.wpr, fp32, a.gran);
+      const int G = class_pairs(cls, a.wpr, fp32, a.gran, a.M);
       const int64_t local = u - uo[b], grp = local / nch, ch = local % nch;
       const int64_t left = (po[b + 1] - po[b]) - grp * G;
       units[u] = make_int4(p, (int)(po[b] + grp * G), (int)(left < G ? left : G), (int)ch);
@@ -1582,9 +1582,9 @@ __global__ void k_export_ip(BaseArgs b, uint16_t* exq, int32_t* exs, int64_t* ex
 // inner product, integer policies: each query's table quantised at every
 // width its pairs use: shift s from the query's span (smallest with
 // (span + hf(s)) >> s <= 2^b - 1), entries (T - min_m + hf(s)) >> s as
-// uint16, or as bytes in the first half of the table's slot (width 4 with
-// one width per pair: ip_bytes); eight entries per thread, read once and
-// written at every width the query needs
+// uint16, or as bytes in the first half of the table's slot (ip_bytes);
+// eight entries per thread, read once and written at every width the query
+// needs
 __global__ void k_ipq(BaseArgs b) {
   const size_t per = (size_t)b.M * kKsub / 8;
   const size_t n = (size_t)b.nq * per;
@@ -2464,7 +2464,7 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
       const int c = fp32 ? 0 : lane_class(sd.M, sd.fixed_bits, sd.gran);
       sa.cls = c;
       sa.counter = ws.counters + ((ph - 1) * (kNCls + 1) + c) * kQueueSlot;
-      sa_lwb = fp32 ? 0 : lane_bits(c, sd.gran);
+      sa_lwb = fp32 ? 0 : lane_bits(c, sd.gran, sd.M);
     } else {
       sa.cls = -1;
       sa.counter = ws.counters + ((ph - 1) * (kNCls + 1) + kNCls) * kQueueSlot;

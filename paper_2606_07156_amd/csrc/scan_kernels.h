@@ -101,7 +101,7 @@ __host__ __device__ constexpr int nib_wpr(int wpr) { return wpr > 1 ? wpr / 2 : 
 __host__ __device__ constexpr int class_wpr(int lwb, int wpr) { return lwb == 4 ? nib_wpr(wpr) : wpr; }
 __host__ __device__ constexpr int unit_pairs(int lwb, int wpr) {
   return lwb < 0 ? (nib_wpr(wpr) * 8 > wpr * 4 ? nib_wpr(wpr) * 8 : wpr * 4)
-                 : (lwb == 0 ? wpr : class_wpr(lwb, wpr) * (32 / lwb));
+                 : class_wpr(lwb, wpr) * lane_fields(lwb);
 }
 
 // row stride (int16 elements) of the integer residuals in LDS: each row is
@@ -136,10 +136,11 @@ __host__ __device__ inline ScanLds scan_lds_layout(int G, int wpr, int M, int d,
   return L;
 }
 
-template <int LWB>  // lane bits 4/8/16/32, 0 = FP32 LUT
+template <int LWB>  // lane bits 4/8/16/32, kLwByte, kLwHalf, 0 = FP32 LUT
 struct Lane {
-  static constexpr int W = LWB ? 32 / LWB : 1;
-  static constexpr uint32_t MASK = LWB == 32 || LWB == 0 ? 0xFFFFFFFFu : ((1u << LWB) - 1);
+  static constexpr int W = lane_fields(LWB);
+  static constexpr int EB = 32 / W;  // entry bits
+  static constexpr uint32_t MASK = EB == 32 ? 0xFFFFFFFFu : ((1u << EB) - 1);
 };
 
 // where pair g of a work unit sits in a LUT row: word and field.  The 8-bit
@@ -472,9 +473,9 @@ __device__ __forceinline__ void lut_mpair(const ScanArgs& a, char* lds, const Sc
           wv8[gt] = qv[0] | (qv[1] << 8) | (qv[2] << 16) | (qv[3] << 24);
           if (gt == NGT - 1)  // words 2 h, 2 h + 1 (h = kg & 1): one 8-byte store
             *reinterpret_cast<u32x2*>(dst + 2 * (kg & 1)) = (u32x2){wv8[0], wv8[1]};
-        } else if constexpr (LWB == 8) {
+        } else if constexpr (LWB == 8 || LWB == kLwByte) {
           dst[g0 >> 2] = qv[0] | (qv[1] << 8) | (qv[2] << 16) | (qv[3] << 24);
-        } else if constexpr (LWB == 16) {
+        } else if constexpr (LWB == 16 || LWB == kLwHalf) {
           const int w0 = g0 >> 1;
           if (w0 + 1 < WPR)
             *reinterpret_cast<u32x2*>(dst + w0) = (u32x2){qv[0] | (qv[1] << 16), qv[2] | (qv[3] << 16)};
@@ -542,7 +543,13 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
   // kWideChunk subspaces are widened into 16-bit lanes (at most 2^15 - 1,
   // guard bit 15) between chunks
   constexpr bool NIB = LWB == 4;
-  const uint32_t SMASK = NIB ? 0x7FFFu : MASK;
+  // byte entries with 16-bit sums, 16-bit entries with 32-bit sums: acc adds
+  // whole words (modulo 2^32) and accb the odd fields alone, which is what the
+  // even fields' sums are recovered with after the last subspace: three (two)
+  // VALU operations per row read for four (two) pairs, as many per pair as
+  // lanes of the sums' width take, and half the row reads
+  constexpr bool B8 = LWB == kLwByte, H16 = LWB == kLwHalf;
+  const uint32_t SMASK = NIB || B8 ? 0x7FFFu : (H16 ? 0xFFFFFFFFu : MASK);
   int32_t* pq = reinterpret_cast<int32_t*>(lds + L.pq);
   int32_t* pb = reinterpret_cast<int32_t*>(lds + L.pb);
   int32_t* ps = reinterpret_cast<int32_t*>(lds + L.ps);
@@ -783,8 +790,8 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
           wc[1] += (uint64_t)nlive;
           wc[2] += (uint64_t)(np_u - nlive);
           // what the unit reads: its chunk's codes once and the live pairs'
-          // quantised tables (bytes for the 4-bit class, else uint16)
-          if (nlive) wc[3] += (uint64_t)((v1 - v0) * M) + (uint64_t)nlive * M * kKsub * (LWB == 4 ? 1 : 2);
+          // quantised tables (bytes for the 4-bit and byte classes, else uint16)
+          if (nlive) wc[3] += (uint64_t)((v1 - v0) * M) + (uint64_t)nlive * M * kKsub * (NIB || B8 ? 1 : 2);
         }
         if (!nlive) {
           fetch_next();
@@ -841,7 +848,23 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
 #pragma unroll
                   for (int i = 0; i < 4; ++i) wds[4 * j + i][w] = t4[0][i] | (t4[1][i] << 4);
                 }
-            } else if constexpr (!BY && LWB == 16) {
+            } else if constexpr (BY && B8) {
+              // byte entries of the word's four pairs: a 4 x 4 byte transpose
+              // for each four entries
+#pragma unroll
+              for (int w = 0; w < WPR; ++w)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                  const uint32_t pa = xs[u][4 * w + 0][j], pb2 = xs[u][4 * w + 1][j];
+                  const uint32_t pc = xs[u][4 * w + 2][j], pd = xs[u][4 * w + 3][j];
+                  const uint32_t ab0 = byte_perm(pb2, pa, 0x05010400u), ab1 = byte_perm(pb2, pa, 0x07030602u);
+                  const uint32_t cd0 = byte_perm(pd, pc, 0x05010400u), cd1 = byte_perm(pd, pc, 0x07030602u);
+                  wds[4 * j + 0][w] = byte_perm(cd0, ab0, 0x05040100u);
+                  wds[4 * j + 1][w] = byte_perm(cd0, ab0, 0x07060302u);
+                  wds[4 * j + 2][w] = byte_perm(cd1, ab1, 0x05040100u);
+                  wds[4 * j + 3][w] = byte_perm(cd1, ab1, 0x07060302u);
+                }
+            } else if constexpr (!BY && (LWB == 16 || H16)) {
               // uint16 entries of two pairs: one byte permute per word
 #pragma unroll
               for (int w = 0; w < WPR; ++w)
@@ -861,7 +884,7 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
                     const u32x4 x = xs[u][PairSlot<LWB, WPR>::pair(w, f)];
                     const uint32_t qv =
                         BY ? (x[k >> 2] >> (8 * (k & 3))) & 0xFFu : (x[k >> 1] >> (16 * (k & 1))) & 0xFFFFu;
-                    wd |= LWB == 32 ? qv : (qv << (f * LWB));
+                    wd |= qv << (f * Lane<LWB>::EB);
                   }
                   wds[k][w] = wd;
                 }
@@ -875,9 +898,10 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
           }
         }
       };
-      // the 4-bit lane class holds width-4 pairs of one width per pair only,
-      // whose tables are bytes (ip_bytes); every other table is uint16
-      if constexpr (LWB == 4) copy(std::true_type{});
+      // the 4-bit class holds width-4 pairs of one width per pair only and the
+      // byte class width-8 ones, whose tables are bytes (ip_bytes); every
+      // other table is uint16
+      if constexpr (NIB || B8) copy(std::true_type{});
       else copy(std::false_type{});
       __syncthreads();
     } else {
@@ -977,7 +1001,7 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
                   for (int t = 0; t < kMaxDsub; ++t)
                     if (t < a.dsub) v += abs((int)ri[g * ri_stride(a.d) + m * a.dsub + t] - cv[t]);
                   const uint32_t qv = (uint32_t)((v + lo[g * M + m]) >> ps[g]);  // lo: hf(s) - min here
-                  wds[w] |= LWB == 32 ? qv : (qv << (f * LWB));
+                  wds[w] |= qv << (f * Lane<LWB>::EB);
                 }
               }
             uint32_t* dst = lut + (size_t)(m * kKsub + j) * WPR;
@@ -1129,15 +1153,16 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
     uint32_t lmin[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) lmin[g] = 0xFFFFFFFFu;
-    // packed thresholds (phases 2, 3) of the 4- and 8-bit lane classes: the
+    // packed thresholds (phases 2, 3) of the 4-bit, byte and 8-bit lane classes: the
     // sums of a LUT word's pairs sit in the 16-bit halves of NTW test words
-    // (8-bit: fields 0, 2 and 1, 3 with guard bit 8; 4-bit: the widened
-    // sums, guard bit 15); a sum passes iff (sigma | guard) - sum keeps the
+    // (8-bit: fields 0, 2 and 1, 3 with guard bit 8; byte: the same with
+    // guard bit 15; 4-bit: the widened sums, guard bit 15); a sum passes iff (sigma | guard) - sum keeps the
     // guard bit, and dead pairs have no guard bit in the mask (never hit)
     constexpr int NTW = NIB ? 4 : 2;
     uint32_t sigw[WPR][NTW], mskw[WPR][NTW];
-    if constexpr (PHASE >= 2 && (LWB == 8 || NIB)) {
-      const uint32_t top = NIB ? 0x7FFFu : 255u, guard = NIB ? 0x8000u : 0x100u;
+    constexpr bool PACKED = LWB == 8 || NIB || B8;
+    if constexpr (PHASE >= 2 && PACKED) {
+      const uint32_t top = NIB || B8 ? 0x7FFFu : 255u, guard = NIB || B8 ? 0x8000u : 0x100u;
 #pragma unroll
       for (int w = 0; w < WPR; ++w)
 #pragma unroll
@@ -1197,8 +1222,9 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
       for (int pv = 0; pv < PV; ++pv) {
       const int64_t v = vb + tid + pv * NT;
       if (v < v1) {
-        // acc: the lanes of each LUT word (4-bit class: the low nibbles, with
-        // the high ones in accb), wz: the 4-bit class's widened sums
+        // acc: the lanes of each LUT word (4-bit, byte and 16-bit-entry classes:
+        // sums of whole words, with the high nibbles or odd fields alone in
+        // accb), wz: the 4-bit class's widened sums
         uint32_t acc[WPR], accb[WPR], wz[WPR][4];
         float accf[WPR];
 #pragma unroll
@@ -1233,8 +1259,14 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
               if constexpr (FP) {
                 accf[w] += __uint_as_float(x[k][w]);
               } else if constexpr (NIB) {
-                acc[w] += x[k][w] & 0x0F0F0F0Fu;
+                acc[w] += x[k][w];
                 accb[w] += (x[k][w] >> 4) & 0x0F0F0F0Fu;
+              } else if constexpr (B8) {
+                acc[w] += x[k][w];
+                accb[w] += byte_perm(0u, x[k][w], 0x0C030C01u);  // bytes 1 and 3
+              } else if constexpr (H16) {
+                acc[w] += x[k][w];
+                accb[w] += x[k][w] >> 16;
               } else {
                 acc[w] += x[k][w];
               }
@@ -1245,8 +1277,9 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
               // low- and high-nibble words into the 16-bit halves of four
 #pragma unroll
               for (int w = 0; w < WPR; ++w) {
-                wz[w][0] += acc[w] & 0x00FF00FFu;
-                wz[w][1] += (acc[w] >> 8) & 0x00FF00FFu;
+                const uint32_t lo = acc[w] - (accb[w] << 4);  // whole words less 16 times the high nibbles
+                wz[w][0] += lo & 0x00FF00FFu;
+                wz[w][1] += (lo >> 8) & 0x00FF00FFu;
                 wz[w][2] += accb[w] & 0x00FF00FFu;
                 wz[w][3] += (accb[w] >> 8) & 0x00FF00FFu;
                 acc[w] = 0;
@@ -1271,6 +1304,10 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
             stepn(One{}, &c4, m4);
           }
         }
+        if constexpr (B8 || H16) {
+#pragma unroll
+          for (int w = 0; w < WPR; ++w) acc[w] -= accb[w] << Lane<LWB>::EB;  // the even fields' sums
+        }
         auto emit = [&](int g, uint32_t S) {
           const int q = pq[g];
           uint64_t key;
@@ -1285,13 +1322,14 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
             a.cid[(size_t)q * a.capq + pos] = id;
           }
         };
-        // the test word t of LUT word w (8-bit: fields 0, 2 / 1, 3; 4-bit:
-        // the widened sums)
+        // the test word t of LUT word w (8-bit and byte: fields 0, 2 / 1, 3;
+        // 4-bit: the widened sums)
         auto tword = [&](int w, int t) -> uint32_t {
           if constexpr (NIB) return wz[w][t];
+          else if constexpr (B8) return t ? accb[w] : acc[w];
           else return t ? (acc[w] >> 8) & 0x00FF00FFu : acc[w] & 0x00FF00FFu;
         };
-        if constexpr (PHASE >= 2 && (LWB == 8 || NIB)) {
+        if constexpr (PHASE >= 2 && PACKED) {
           // every sum of a LUT word tested against its threshold at once, in
           // the 16-bit halves of its test words
 #pragma unroll
@@ -1315,6 +1353,8 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
             const int w = PairSlot<LWB, WPR>::word(g), f = PairSlot<LWB, WPR>::field(g);
             uint32_t S;
             if constexpr (FP) S = fkey(accf[w]);
+            else if constexpr (B8) S = (tword(w, f & 1) >> (16 * (f >> 1))) & 0xFFFFu;
+            else if constexpr (H16) S = f ? accb[w] : acc[w];
             else if constexpr (NIB) S = (wz[w][test_word<LWB, WPR>(g)] >> (16 * test_half<LWB, WPR>(g))) & 0xFFFFu;
             else S = LWB == 32 ? acc[w] : ((acc[w] >> (f * LWB)) & MASK);
             if (PHASE == 1) {
@@ -1500,10 +1540,13 @@ __global__ __launch_bounds__(NT, scan_min_blocks(MT, NT))
       if (tid == 0 && next_u < total) next_unit = a.units[locate(next_u, next_cls)];
     };
     const int cls = s_cls;
-    if (cls == 0 && !a.gran) scan_unit<4, MT, PHASE, DT, NR, NT>(a, lds, L, own, s_unit, fetch);
-    else if (cls == 0) scan_unit<8, MT, PHASE, DT, NR, NT>(a, lds, L, own, s_unit, fetch);
-    else if (cls == 1) scan_unit<16, MT, PHASE, DT, NR, NT>(a, lds, L, own, s_unit, fetch);
-    else scan_unit<32, MT, PHASE, DT, NR, NT>(a, lds, L, own, s_unit, fetch);
+    const int lwb = lane_bits(cls, a.gran, M);
+    if (lwb == 4) scan_unit<4, MT, PHASE, DT, NR, NT>(a, lds, L, own, s_unit, fetch);
+    else if (lwb == 8) scan_unit<8, MT, PHASE, DT, NR, NT>(a, lds, L, own, s_unit, fetch);
+    else if (lwb == 16) scan_unit<16, MT, PHASE, DT, NR, NT>(a, lds, L, own, s_unit, fetch);
+    else if (lwb == kLwHalf) scan_unit<kLwHalf, MT, PHASE, DT, NR, NT>(a, lds, L, own, s_unit, fetch);
+    else if (lwb == 32) scan_unit<32, MT, PHASE, DT, NR, NT>(a, lds, L, own, s_unit, fetch);
+    else if constexpr (MT == 0 || byte_class(MT)) scan_unit<kLwByte, MT, PHASE, DT, NR, NT>(a, lds, L, own, s_unit, fetch);
     __syncthreads();
     if (tid == 0) {
       s_u = next_u;

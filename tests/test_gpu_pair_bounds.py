@@ -26,7 +26,7 @@ def random_index(seed, M, dsub, nlist=40, n=6000, metric="l2", scale=3.0, grid_e
                 centroids=(r.standard_normal((nlist, d)) * scale).astype(np.float32),
                 codebook=r.standard_normal((M, 256, dsub)).astype(np.float32), list_offsets=off, ids=ids,
                 codes=r.integers(0, 256, (n, M)).astype(np.uint8),
-                radq=r.integers(1, 500, nlist).astype(np.int32))
+                radq=r.integers(1, 500, nlist).astype(np.int32), list_sizes=np.diff(off).astype(np.int32))
 
 
 # (pairs, nprobe): one pair, around a tile of 32, ragged tiles, and batches of
