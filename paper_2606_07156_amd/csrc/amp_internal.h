@@ -180,7 +180,6 @@ struct Workspace {
   uint16_t* iptq = nullptr;    // [nq][4][M][256] quantised tables, one per width the query uses
   int32_t* ipsh = nullptr;     // [nq][4] their shifts
   int32_t* ipmask = nullptr;   // [nq] widths the query's pairs use (bit b/4 - 1)
-  uint8_t* retry = nullptr;    // [nq] query takes part in the phase-2 re-run
   int64_t* tau_id = nullptr;   // [nq] id part of the re-run's bound
   // integer cluster locating (laid out when the index has a sub-space map)
   int8_t* clq = nullptr;       // [nq][S][Kp] query codes
@@ -200,7 +199,7 @@ struct Workspace {
   int64_t* unitoff = nullptr;  // [2][NB+1]
   int32_t* sorted = nullptr;   // [2][nq*npmax]
   uint32_t* counters = nullptr;// [2][kNCls+1][kQueueSlot] unit counters
-  int32_t* flags = nullptr;    // [4]: error bits, phase-2 re-run requested (two rounds), -
+  int32_t* flags = nullptr;    // [4]: error bits, work units of the phase-2 re-runs (two rounds), -
   int32_t* status = nullptr;   // [1] device-side status word of the last search
   uint64_t* work = nullptr;    // [4]: phase-2 code bytes scanned, live pairs, dead pairs, -
   // outputs staged for host mode

@@ -675,7 +675,6 @@ static amp_status lay_out(const amp_index* ix, Workspace& w, size_t nq, size_t n
     AMP_TAKE(&w.clcn, cl ? (size_t)ix->nlist * S * 2 : 1);
     w.cap_cl = cl_layout_key(ix);
   }
-  AMP_TAKE(&w.retry, nq);
   AMP_TAKE(&w.tau_id, nq);
   AMP_TAKE(&w.ccount, nq);
   AMP_TAKE(&w.ckey, nq * capq);
@@ -1237,7 +1236,7 @@ amp_status search_on(amp_index* ix, Workspace& w, const void* queries, int64_t n
     uint32_t mx = 0;
     for (uint32_t c : cc) sum += c, mx = std::max(mx, c);
     fprintf(stderr, "[amp] candidates per query: mean %.1f max %u (capacity %zu)\n", sum / nq, mx, capq);
-    if (host) fprintf(stderr, "[amp] phase-2 re-runs: %d %d\n", flags[1], flags[2]);
+    if (host) fprintf(stderr, "[amp] phase-2 re-runs: %d %d\n", flags[1] != 0, flags[2] != 0);
     // pairs, work units and scanned vectors per phase and lane class
     const int ncls = pol->kind == AMP_POLICY_FP32 ? 1 : kNCls;
     const size_t NB = (size_t)ncls * ix->nlist;

@@ -878,12 +878,6 @@ __device__ __forceinline__ bool pair_live(const QueueArgs& a, size_t i) {
   return key <= a.tau[i / a.npmax];
 }
 
-__device__ __forceinline__ int pair_class(int bits, int M, int gran) {
-  if (bits == 32) return 0;
-  if (bits == 4 && gran == 0 && M <= 2184) return 0;  // 4-bit entries, sums widened (lane_class)
-  uint64_t top = (uint64_t)M * ((1ull << bits) - 1);
-  return top <= 0xFFull ? 0 : (top <= 0xFFFFull ? 1 : 2);
-}
 // pairs of a work unit: the LUT words of its class's rows times their fields
 __device__ __forceinline__ int class_pairs(int cls, int wpr, bool fp32, int gran, int M) {
   return fp32 ? wpr : unit_pairs(lane_bits(cls, gran, M), wpr);
@@ -1070,10 +1064,10 @@ __global__ void k_qunits(QueueArgs a, int fp32) {
 // select).
 __global__ __launch_bounds__(256) void k_tau_wave(uint32_t* ccount, const uint64_t* ckey, uint64_t* tau,
                                                   const int32_t* kq, int kconst, int nq, size_t capq,
-                                                  int32_t* any_retry) {
+                                                  int32_t* nrerun) {
   const int lane = threadIdx.x & 63;
   const int q = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (q == 0 && lane < 2) any_retry[lane] = 0;  // no phase-2 re-run requested yet (two rounds)
+  if (q == 0 && lane < 2) nrerun[lane] = 0;  // no work units of a phase-2 re-run yet (two rounds)
   if (q >= nq) return;
   const uint32_t cnt = ccount[q];
   const int n = (int)(cnt < capq ? cnt : capq);
@@ -1143,49 +1137,85 @@ __global__ __launch_bounds__(256) void k_tau(uint32_t* ccount, const uint64_t* c
 
 // after phase 2: a query whose candidates overflowed the buffer takes the
 // k-th smallest (distance, id) of the candidates kept (distinct vectors, each
-// within its old bound) as a tighter bound and is marked for a re-run of
-// phase 2; the others are unmarked.  Block 0 also rewinds the phase-2 unit counters.
-__global__ __launch_bounds__(256) void k_retry(uint32_t* ccount, const uint64_t* ckey, const int64_t* cid,
-                                               uint64_t* tau, int64_t* tau_id, const int32_t* kq, int kconst, int nq,
-                                               size_t capq, uint8_t* retry, int32_t* any_retry, uint32_t* counters,
-                                               int ncounters) {
+// within its old bound) as a tighter bound, and its pairs still within it
+// become the work units of a re-run of phase 2, one pair and list chunk each
+// (in the phase-1 unit and pair arrays, which are free by then).  Block 0
+// also rewinds the phase-2 unit counters.
+// (Re-running the phase-2 queue itself with the other queries masked out made
+// the re-run pay for claiming and skipping every unit, and for scanning the
+// other pairs' lanes: 640 us and 210 us for the bounds by full sorts, for a
+// few queries of a 4096-query batch at 5M x 768; 154 and 49 us this way.)
+struct RetryArgs {
+  uint32_t* ccount;
+  const uint64_t* ckey;
+  const int64_t* cid;
+  uint64_t* tau;
+  int64_t* tau_id;
+  const int32_t* kq;
+  int kconst, nq, ncounters;
+  size_t capq;
+  int32_t* nrerun;       // this round's unit count
+  uint32_t* counters;
+  int4* units;           // this round's units
+  int32_t* sorted;       // [pair] = pair
+};
+
+__global__ __launch_bounds__(256) void k_retry(RetryArgs r, QueueArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   uint64_t* keys = reinterpret_cast<uint64_t*>(lds);
-  int64_t* vals = reinterpret_cast<int64_t*>(lds + capq * 8);
-  int* s_n = reinterpret_cast<int*>(lds + capq * 16);
+  uint64_t* vals = reinterpret_cast<uint64_t*>(lds + r.capq * 8);   // ids of the keys equal to the k-th smallest
+  uint32_t* hist = reinterpret_cast<uint32_t*>(lds + r.capq * 16);  // [256]
+  uint32_t* sel = hist + 256;                                        // [2]
+  int* s_n = reinterpret_cast<int*>(sel + 2);
   int* s_q = s_n + 1;  // [blockDim.x]
   if (blockIdx.x == 0)
-    for (int i = threadIdx.x; i < ncounters; i += blockDim.x) counters[i] = 0;
+    for (int i = threadIdx.x; i < r.ncounters; i += blockDim.x) r.counters[i] = 0;
   // the workgroup's queries q = blockIdx.x + i * gridDim.x, a thread each:
   // the candidate counts are read side by side (no chain of dependent
-  // loads), and only the overflowed queries go on to the sort
-  for (int64_t base = blockIdx.x; base < nq; base += (int64_t)gridDim.x * blockDim.x) {
+  // loads), and only the overflowed queries go on to the selection
+  for (int64_t base = blockIdx.x; base < r.nq; base += (int64_t)gridDim.x * blockDim.x) {
     const int64_t q = base + (int64_t)threadIdx.x * gridDim.x;
-    bool over = false;
-    if (q < nq) {
-      over = ccount[q] > capq;
-      if (!over) retry[q] = 0;
-    }
+    const bool over = q < r.nq && r.ccount[q] > r.capq;
     if (threadIdx.x == 0) *s_n = 0;
     __syncthreads();
     if (over) s_q[atomicAdd(s_n, 1)] = (int)q;
     __syncthreads();
     const int n = *s_n;
+    __syncthreads();  // s_n counts again below
     for (int t = 0; t < n; ++t) {
-      const int qq = s_q[t];
-      for (size_t i = threadIdx.x; i < capq; i += blockDim.x) {
-        keys[i] = ckey[(size_t)qq * capq + i];
-        vals[i] = cid[(size_t)qq * capq + i];
+      const int qq = s_q[t], nc = (int)r.capq;
+      const int kk = r.kq ? r.kq[qq] : r.kconst;
+      for (int i = threadIdx.x; i < nc; i += blockDim.x) keys[i] = r.ckey[(size_t)qq * r.capq + i];
+      if (threadIdx.x == 0) sel[0] = *s_n = 0;
+      __syncthreads();
+      const uint64_t key = block_select_u64(keys, nc, kk, hist, sel);
+      if (threadIdx.x == 0) sel[0] = 0;
+      __syncthreads();
+      // its id: the ids of the equal keys, of which (k - smaller keys) are taken
+      for (int i = threadIdx.x; i < nc; i += blockDim.x) {
+        if (keys[i] < key) atomicAdd(&sel[0], 1u);
+        else if (keys[i] == key) vals[atomicAdd(s_n, 1)] = ikey(r.cid[(size_t)qq * r.capq + i]);
       }
       __syncthreads();
-      block_bitonic_u64_i64(keys, vals, (int)capq);
-      const int kk = kq ? kq[qq] : kconst;
+      const int below = (int)sel[0], neq = *s_n;
+      __syncthreads();
+      const int64_t id = ikey_val(block_select_u64(vals, neq, kk - below, hist, sel));
       if (threadIdx.x == 0) {
-        tau[qq] = keys[kk - 1];
-        tau_id[qq] = vals[kk - 1];
-        ccount[qq] = 0;
-        retry[qq] = 1;
-        *any_retry = 1;
+        r.tau[qq] = key;
+        r.tau_id[qq] = id;
+        r.ccount[qq] = 0;
+      }
+      // the pairs that may still hold a candidate
+      for (int j = threadIdx.x; j < a.npmax; j += blockDim.x) {
+        const size_t i = (size_t)qq * a.npmax + j;
+        const int p = a.probes[i];
+        if (p < 0) continue;
+        if (a.pbase && (a.fkeys ? (uint64_t)a.pbase[i] : ikey(a.pbase[i])) > key) continue;
+        const int nch = (int)((a.offsets[p + 1] - a.offsets[p] + a.chunk[1] - 1) / a.chunk[1]);
+        if (!nch) continue;
+        const int u = atomicAdd(r.nrerun, nch);
+        r.sorted[i] = (int32_t)i;
+        for (int c = 0; c < nch; ++c) r.units[u + c] = make_int4(p, (int)i, 1, c);
       }
       __syncthreads();  // the LDS is reused by the next query
     }
@@ -2439,9 +2469,8 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
   sa.kmax = sd.kmax;
   sa.chunk = sd.chunk;  // per phase below
   sa.capq = sd.capq;
-  sa.retry = nullptr;
   sa.tau_id = nullptr;
-  sa.any_retry = nullptr;
+  sa.nrerun = nullptr;
   sa.work = nullptr;
   sa.steal = sd.queue;
   sa.iptab = ws.iptab;
@@ -2492,18 +2521,23 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
       // each with a tighter bound (the scan kernels return at once when no
       // query takes part); each re-run shrinks a query's candidate count by
       // about k / capq
-      const size_t rlds = sd.capq * 16 + 4 * (1 + 256);  // sort rows + overflowed-query list
+      const size_t rlds = sd.capq * 16 + 4 * (256 + 2 + 1 + 256);  // keys, ids, digit counts, selection, query list
       err = hipFuncSetAttribute(kaddr(k_retry), hipFuncAttributeMaxDynamicSharedMemorySize, (int)rlds);
       if (err != hipSuccess) return err;
       ScanArgs sr = sa;
-      sr.retry = ws.retry;
       sr.tau_id = ws.tau_id;
+      sr.sorted = ws.sorted;
+      sr.units = ws.units;
+      RetryArgs ra{ws.ccount, ws.ckey, ws.cid, ws.tau, ws.tau_id, ws.kq, sd.kconst, sd.nq, (kNCls + 1) * kQueueSlot,
+                   sd.capq, nullptr, ws.counters + (kNCls + 1) * kQueueSlot, ws.units, ws.sorted};
+      QueueArgs qr = qa;
+      if (early) {
+        qr.pbase = ws.pbase;
+        qr.fkeys = fp32 ? 1 : 0;
+      }
       for (int rr = 0; rr < sd.reruns; ++rr) {
-        sr.any_retry = ws.flags + 1 + rr;  // one flag per round
-        hipLaunchKernelGGL(k_retry, dim3(sd.nq < 256 ? sd.nq : 256), dim3(256), rlds, st, ws.ccount, ws.ckey,
-                           ws.cid, ws.tau, ws.tau_id, ws.kq, sd.kconst, sd.nq, sd.capq, ws.retry,
-                           ws.flags + 1 + rr, ws.counters + (kNCls + 1) * kQueueSlot,
-                           (kNCls + 1) * kQueueSlot);
+        sr.nrerun = ra.nrerun = ws.flags + 1 + rr;  // a unit count per round
+        hipLaunchKernelGGL(k_retry, dim3(sd.nq < 256 ? sd.nq : 256), dim3(256), rlds, st, ra, qr);
         // phase 3: the phase-2 scan's re-run (its own kernel symbol)
         if ((err = launch_scan(sa_lwb, 3, dt, sd.wpr, sr, st)) != hipSuccess) return err;
       }

@@ -29,9 +29,8 @@ struct ScanArgs {
   uint64_t* ckey;
   int64_t* cid;
   int32_t* flags;
-  const uint8_t* retry;     // phase 3 (re-run of phase 2): queries taking part
   const int64_t* tau_id;    // phase 3: id of the bound's (distance, id) key
-  const int32_t* any_retry; // phase 3: non-zero if any query takes part
+  const int32_t* nrerun;    // phase 3 (re-run of phase 2): its work units (one pair each)
   uint64_t* work;           // phase 2 work counters (code bytes scanned, live pairs, dead pairs) or null
   // inner product: the query's table built once per query (integer: exact T
   // with its row minima and span; FP32 policy: FP32 dot products), and the
@@ -176,6 +175,14 @@ __host__ __device__ constexpr int test_word(int g) {
 template <int LWB, int WPR>
 __host__ __device__ constexpr int test_half(int g) {
   return LWB == 4 ? ((g & 3) >> 1) : (PairSlot<LWB, WPR>::field(g) >> 1);
+}
+
+// lane-width class of a pair's LUT width (32: the FP32 policy's only class)
+__device__ __forceinline__ int pair_class(int bits, int M, int gran) {
+  if (bits == 32) return 0;
+  if (bits == 4 && gran == 0 && M <= 2184) return 0;  // 4-bit entries, sums widened (lane_class)
+  uint64_t top = (uint64_t)M * ((1ull << bits) - 1);
+  return top <= 0xFFull ? 0 : (top <= 0xFFFFull ? 1 : 2);
 }
 
 // LDS-address-space views: the scan kernels declare no static LDS, so their
@@ -581,20 +588,6 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
         pb[tid] = 16;
       }
     }
-    if (PHASE == 3) {
-      // re-run: a unit with no pair of a re-run query is skipped whole (the
-      // vote goes through a control word of the dynamic LDS: the scan
-      // kernels use no static LDS)
-      int& s_part = *reinterpret_cast<int*>(lds + L.ctl + 8);
-      if (tid == 0) s_part = 0;
-      __syncthreads();
-      if (tid < np_u && a.retry[pq[tid]]) s_part = 1;
-      __syncthreads();
-      if (!s_part) {
-        fetch_next();
-        return;
-      }
-    }
     __syncthreads();
     // ---- RC: residuals (FP32, then onto the grid for integer policies)
     // (inner product: the query itself, on the grid for integer policies)
@@ -640,7 +633,7 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
     auto pair_threshold = [&](int g) -> bool {
       uint32_t sig = 0;
       bool live = false;
-      if (g < np_u && (PHASE != 3 || a.retry[pq[g]])) {
+      if (g < np_u) {
         const uint64_t tk = a.tau[pq[g]];
         live = true;
         if (tk == ~0ull) {
@@ -1438,12 +1431,12 @@ __global__ __launch_bounds__(NT, scan_min_blocks(MT, NT))
     if (threadIdx.x == 0) atomicOr(&a.flags[0], 16);
     return;
   }
-  if (PHASE == 3 && *a.any_retry == 0) return;  // re-run of phase 2 with nothing to do
+  if (PHASE == 3 && *a.nrerun == 0) return;  // re-run of phase 2 with nothing to do
   int& s_u = *reinterpret_cast<int*>(lds + L.ctl);
   int4& s_unit = *reinterpret_cast<int4*>(lds + L.ctl + 16);
   const int tid = threadIdx.x;
-  const int64_t ub = a.unitoff[(size_t)a.cls * a.nlist];
-  const int64_t ue = a.unitoff[(size_t)(a.cls + 1) * a.nlist];
+  const int64_t ub = PHASE == 3 ? 0 : a.unitoff[(size_t)a.cls * a.nlist];
+  const int64_t ue = PHASE == 3 ? *a.nrerun : a.unitoff[(size_t)(a.cls + 1) * a.nlist];
   const int own_j = tid % kKsub, own_m0 = tid / kKsub;
   const bool owner = tid < MPAR * kKsub;
   Owned<WPR, CRES ? MT : 0> own;
@@ -1501,7 +1494,7 @@ __global__ __launch_bounds__(NT, scan_min_blocks(MT, NT))
     if (threadIdx.x == 0) atomicOr(&a.flags[0], 16);
     return;
   }
-  if (PHASE == 3 && *a.any_retry == 0) return;  // re-run of phase 2 with nothing to do
+  if (PHASE == 3 && *a.nrerun == 0) return;  // re-run of phase 2 with nothing to do
   int& s_u = *reinterpret_cast<int*>(lds + L.ctl);
   int& s_cls = *reinterpret_cast<int*>(lds + L.ctl + 4);
   int4& s_unit = *reinterpret_cast<int4*>(lds + L.ctl + 16);
@@ -1509,9 +1502,13 @@ __global__ __launch_bounds__(NT, scan_min_blocks(MT, NT))
   const int64_t* uo = a.unitoff;
   const int64_t n2 = uo[3 * (size_t)a.nlist] - uo[2 * (size_t)a.nlist];
   const int64_t n1 = uo[2 * (size_t)a.nlist] - uo[a.nlist];
-  const int64_t total = uo[3 * (size_t)a.nlist] - uo[0];
+  const int64_t total = PHASE == 3 ? *a.nrerun : uo[3 * (size_t)a.nlist] - uo[0];
   // unit number in launch order -> (class, row of the class-major unit table)
   auto locate = [&](int64_t u, int& cls) -> int64_t {
+    if (PHASE == 3) {  // (one pair per unit: the class is its width's)
+      cls = pair_class(a.pbits[a.sorted[a.units[u].y]], M, a.gran);
+      return u;
+    }
     if (u < n2) { cls = 2; return uo[2 * (size_t)a.nlist] + u; }
     if (u < n2 + n1) { cls = 1; return uo[a.nlist] + (u - n2); }
     cls = 0;
