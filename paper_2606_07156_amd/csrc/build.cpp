@@ -15,8 +15,11 @@
 //    or residual magnitude (inner product: also centroid and vector
 //    magnitudes) within the grid's largest value (255, or 448 for e4m3);
 //    integer data: h = 1;  radius max ||x - c|| in grid units, rounded.
-// Distances and assignments run on the GPU (FP32 MFMA); sums and the final
-// layout on the host in FP64 / integers.
+// Distances, assignments, the means' FP64 sums (in row order) and the radius
+// run on the GPU (build_kernels.hip), the residual codebook's k-means for all
+// subspaces side by side; seeded choices and the final layout on the host.  A
+// k-means in which a cluster runs empty is repeated on the host, which reseeds
+// it.
 #include <algorithm>
 #include <atomic>
 #include <cmath>
@@ -28,7 +31,7 @@
 #include <unordered_set>
 #include <vector>
 
-#include "amp_internal.h"
+#include "build_kernels.h"
 
 namespace amp {
 namespace {
@@ -92,40 +95,95 @@ struct Dev {  // device scratch of the build, freed on scope exit
     if (e_ != hipSuccess) return set_error(AMP_EDEVICE, "%s: %s", #call, hipGetErrorString(e_)); \
   } while (0)
 
-// k-means of rows [n][dd] (host, contiguous) into k centroids; returns FP32
-// centroids [k][dd]
-amp_status kmeans(const float* rows, int64_t n, int dd, int k, int iters, uint64_t seed, hipStream_t st,
-                  std::vector<float>& out) {
-  const int64_t ntrain = std::min<int64_t>(n, (int64_t)256 * k);
-  // seeded sample: the ntrain rows of smallest hash, in row order
+// the seeded sample of n rows: the ntrain rows of smallest hash, in row order
+std::vector<int64_t> sample_rows(int64_t n, int64_t ntrain, uint64_t seed) {
   std::vector<int64_t> sample(n);
   std::iota(sample.begin(), sample.end(), 0);
   if (ntrain < n) {
     std::vector<uint64_t> key(n);
-    for (int64_t i = 0; i < n; ++i) key[i] = mix64(seed * 0x100000001B3ull ^ (uint64_t)i);
+    parallel_for(n, [&](int64_t i0, int64_t i1, int) {
+      for (int64_t i = i0; i < i1; ++i) key[i] = mix64(seed * 0x100000001B3ull ^ (uint64_t)i);
+    });
     std::nth_element(sample.begin(), sample.begin() + ntrain, sample.end(),
                      [&](int64_t a, int64_t b) { return key[a] < key[b] || (key[a] == key[b] && a < b); });
     sample.resize(ntrain);
     std::sort(sample.begin(), sample.end());
   }
-  std::vector<float> S((size_t)ntrain * dd);
-  for (int64_t i = 0; i < ntrain; ++i) std::memcpy(&S[(size_t)i * dd], rows + sample[i] * dd, dd * sizeof(float));
-  // initial centroids: first distinct rows in a seeded order of the sample
-  std::vector<int64_t> perm(ntrain);
-  std::iota(perm.begin(), perm.end(), 0);
+  return sample;
+}
+
+// initial centroids: the first k distinct rows in a seeded order of ntrain
+// rows (fewer distinct rows than k: repeated in turn).  row(i, out) writes
+// row i (dd floats).  The order is looked at from its front only: the 4 k
+// rows of smallest hash, more where they hold too few distinct ones.
+template <typename Row>
+std::vector<int64_t> first_distinct(int64_t ntrain, int dd, int k, uint64_t seed, Row&& row) {
   std::vector<uint64_t> pk(ntrain);
   for (int64_t i = 0; i < ntrain; ++i) pk[i] = mix64((seed + 0x5851F42D4C957F2Dull) ^ (uint64_t)i);
-  std::sort(perm.begin(), perm.end(), [&](int64_t a, int64_t b) { return pk[a] < pk[b] || (pk[a] == pk[b] && a < b); });
-  std::vector<int64_t> picked;
+  const auto less = [&](int64_t a, int64_t b) { return pk[a] < pk[b] || (pk[a] == pk[b] && a < b); };
+  std::vector<int64_t> perm(ntrain), picked;
+  std::iota(perm.begin(), perm.end(), 0);
   std::unordered_set<std::string> seen;
-  for (int64_t i : perm) {
-    std::string b(reinterpret_cast<const char*>(&S[(size_t)i * dd]), dd * sizeof(float));
-    if (!seen.insert(b).second) continue;
-    picked.push_back(i);
-    if ((int)picked.size() == k) break;
+  std::vector<float> x(dd);
+  for (int64_t from = 0, to = std::min<int64_t>(ntrain, 4 * (int64_t)k); from < ntrain && (int)picked.size() < k;
+       from = to, to = std::min<int64_t>(ntrain, 4 * to)) {
+    if (to < ntrain) std::nth_element(perm.begin() + from, perm.begin() + to, perm.end(), less);
+    std::sort(perm.begin() + from, perm.begin() + to, less);
+    for (int64_t j = from; j < to && (int)picked.size() < k; ++j) {
+      row(perm[j], x.data());
+      std::string b(reinterpret_cast<const char*>(x.data()), dd * sizeof(float));
+      if (seen.insert(b).second) picked.push_back(perm[j]);
+    }
   }
   const size_t npk = picked.size();
-  for (size_t i = npk; i < (size_t)k; ++i) picked.push_back(picked[i % npk]);  // fewer distinct rows than k
+  for (size_t i = npk; i < (size_t)k; ++i) picked.push_back(picked[i % npk]);
+  return picked;
+}
+
+// Lloyd iterations on the device for G groups of n rows side by side: row r
+// of group g is dX + r ld + g dd, its k centroids C [g][k][dd] (on entry the
+// initial ones, exact FP32 values).  empty[g] != 0: a cluster of the group ran
+// empty on the way and the group's result is not valid.
+amp_status kmeans_device(const float* dX, int64_t n, int dd, int ld, int G, int k, int iters, hipStream_t st,
+                         std::vector<float>& C, std::vector<int32_t>& empty) {
+  Dev dv;
+  float *dC, *dcn, *dxn;
+  double* dC64;
+  int32_t *da, *o1, *o2, *hist, *de;
+  AMP_BHIP(dv.alloc(&dC, C.size()));
+  AMP_BHIP(dv.alloc(&dC64, C.size()));
+  AMP_BHIP(dv.alloc(&dcn, (size_t)G * k));
+  AMP_BHIP(dv.alloc(&dxn, G == 1 ? n : 1));
+  AMP_BHIP(dv.alloc(&da, (size_t)G * n));
+  AMP_BHIP(dv.alloc(&o1, (size_t)G * n));
+  AMP_BHIP(dv.alloc(&o2, k > 256 ? (size_t)G * n : 1));
+  AMP_BHIP(dv.alloc(&hist, group_hist_words((int)n, G)));
+  AMP_BHIP(dv.alloc(&de, G));
+  empty.assign(G, 0);
+  const std::vector<double> C64(C.begin(), C.end());
+  AMP_BHIP(hipMemcpyAsync(dC, C.data(), C.size() * 4, hipMemcpyHostToDevice, st));
+  AMP_BHIP(hipMemcpyAsync(dC64, C64.data(), C64.size() * 8, hipMemcpyHostToDevice, st));
+  AMP_BHIP(hipMemcpyAsync(de, empty.data(), (size_t)G * 4, hipMemcpyHostToDevice, st));
+  for (int it = 0; it < iters; ++it) {
+    if (G == 1) {
+      AMP_BHIP(launch_assign(dX, n, dd, ld, dC, k, dxn, dcn, da, nullptr, st));
+    } else {
+      AMP_BHIP(launch_sqnorm(dC, (int64_t)G * k, dd, dcn, st));
+      AMP_BHIP(launch_assign_sub(dX, n, dd, ld, G, dC, dcn, da, nullptr, st));
+    }
+    AMP_BHIP(launch_means(dX, (int)n, dd, ld, G, k, da, o1, o2, hist, dC64, dC, de, st));
+  }
+  AMP_BHIP(hipMemcpyAsync(C.data(), dC, C.size() * 4, hipMemcpyDeviceToHost, st));
+  AMP_BHIP(hipMemcpyAsync(empty.data(), de, (size_t)G * 4, hipMemcpyDeviceToHost, st));
+  AMP_BHIP(hipStreamSynchronize(st));
+  return AMP_OK;
+}
+
+// k-means of rows S [ntrain][dd] (host, contiguous) into k centroids from the
+// rows `picked`, means on the host: the definition, and the way of a k-means
+// whose clusters run empty
+amp_status kmeans_host(const std::vector<float>& S, int64_t ntrain, int dd, int k, int iters,
+                       const std::vector<int64_t>& picked, hipStream_t st, std::vector<float>& out) {
   std::vector<double> C((size_t)k * dd);
   for (int c = 0; c < k; ++c)
     for (int t = 0; t < dd; ++t) C[(size_t)c * dd + t] = S[(size_t)picked[c] * dd + t];
@@ -249,88 +307,122 @@ static amp_status amp_index_build_body(const void* base_in, int64_t n, int32_t d
   amp_status s;
   // coarse quantiser
   std::vector<float> C;
-  if ((s = kmeans(base, n, d, nlist, iters, prm->seed, st, C)) != AMP_OK) return s;
+  {
+    const int64_t nt = std::min<int64_t>(n, (int64_t)256 * nlist);
+    const std::vector<int64_t> smp = sample_rows(n, nt, prm->seed);
+    std::vector<float> S((size_t)nt * d);
+    parallel_for(nt, [&](int64_t i0, int64_t i1, int) {
+      for (int64_t i = i0; i < i1; ++i) std::memcpy(&S[(size_t)i * d], base + smp[i] * d, d * sizeof(float));
+    });
+    const std::vector<int64_t> picked = first_distinct(nt, d, nlist, prm->seed, [&](int64_t i, float* x) {
+      std::memcpy(x, &S[(size_t)i * d], d * sizeof(float));
+    });
+    C.resize((size_t)nlist * d);
+    for (int c = 0; c < nlist; ++c) std::memcpy(&C[(size_t)c * d], &S[(size_t)picked[c] * d], d * sizeof(float));
+    std::vector<int32_t> empty;
+    {
+      Dev dv;
+      float* dS;
+      AMP_BHIP(dv.alloc(&dS, S.size()));
+      AMP_BHIP(hipMemcpyAsync(dS, S.data(), S.size() * sizeof(float), hipMemcpyHostToDevice, st));
+      if ((s = kmeans_device(dS, nt, d, d, 1, nlist, iters, st, C, empty)) != AMP_OK) return s;
+    }
+    if (empty[0] && (s = kmeans_host(S, nt, d, nlist, iters, picked, st, C)) != AMP_OK) return s;
+  }
   if (prm->integer_data)
     for (float& v : C) v = std::nearbyint(v);
+  // the rows whose residuals train the codebook: a seeded sample
+  const int64_t nr = std::min<int64_t>(n, (int64_t)256 * kKsub);
+  const std::vector<int64_t> rs = sample_rows(n, nr, prm->seed + 1);
   // assign every vector (chunks on the device) and keep its residual sample
   const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>(n, (int64_t)(1 << 28) / (4 * d)));
   std::vector<int32_t> a(n);
-  {
-    Dev dv;
-    float *dX, *dC, *dxn, *dcn;
-    int32_t* da;
-    AMP_BHIP(dv.alloc(&dX, (size_t)chunk * d));
-    AMP_BHIP(dv.alloc(&dC, C.size()));
-    AMP_BHIP(dv.alloc(&dxn, chunk));
-    AMP_BHIP(dv.alloc(&dcn, nlist));
-    AMP_BHIP(dv.alloc(&da, chunk));
-    AMP_BHIP(hipMemcpyAsync(dC, C.data(), C.size() * 4, hipMemcpyHostToDevice, st));
-    for (int64_t c0 = 0; c0 < n; c0 += chunk) {
-      const int64_t m = std::min(chunk, n - c0);
-      AMP_BHIP(hipMemcpyAsync(dX, base + c0 * d, (size_t)m * d * 4, hipMemcpyHostToDevice, st));
-      AMP_BHIP(launch_assign(dX, m, d, d, dC, nlist, dxn, dcn, da, nullptr, st));
-      AMP_BHIP(hipMemcpyAsync(a.data() + c0, da, m * 4, hipMemcpyDeviceToHost, st));
-    }
-    AMP_BHIP(hipStreamSynchronize(st));
+  Dev dv;
+  float *dX, *dR, *dC, *dxn, *dcn, *dsmp;
+  int32_t *da, *drow;
+  AMP_BHIP(dv.alloc(&dX, (size_t)chunk * d));
+  AMP_BHIP(dv.alloc(&dR, (size_t)chunk * d));
+  AMP_BHIP(dv.alloc(&dC, C.size()));
+  AMP_BHIP(dv.alloc(&dxn, chunk));
+  AMP_BHIP(dv.alloc(&dcn, std::max<size_t>(nlist, (size_t)M * kKsub)));
+  AMP_BHIP(dv.alloc(&da, chunk));
+  AMP_BHIP(dv.alloc(&dsmp, (size_t)nr * d));
+  AMP_BHIP(dv.alloc(&drow, nr));
+  AMP_BHIP(hipMemcpyAsync(dC, C.data(), C.size() * 4, hipMemcpyHostToDevice, st));
+  std::vector<int32_t> rows(nr);  // sampled rows relative to their chunk
+  for (int64_t c0 = 0, j0 = 0; c0 < n; c0 += chunk) {
+    const int64_t m = std::min(chunk, n - c0);
+    int64_t j1 = j0;
+    for (; j1 < nr && rs[j1] < c0 + m; ++j1) rows[j1] = (int32_t)(rs[j1] - c0);
+    AMP_BHIP(hipMemcpyAsync(dX, base + c0 * d, (size_t)m * d * 4, hipMemcpyHostToDevice, st));
+    AMP_BHIP(hipMemcpyAsync(drow + j0, rows.data() + j0, (size_t)(j1 - j0) * 4, hipMemcpyHostToDevice, st));
+    AMP_BHIP(launch_assign(dX, m, d, d, dC, nlist, dxn, dcn, da, nullptr, st));
+    AMP_BHIP(launch_gather_residual(dX, da, dC, drow + j0, j1 - j0, d, dsmp + j0 * d, st));
+    AMP_BHIP(hipMemcpyAsync(a.data() + c0, da, m * 4, hipMemcpyDeviceToHost, st));
+    j0 = j1;
   }
-  // residual codebook: k-means per subspace on a seeded sample of residuals
-  const int64_t nr = std::min<int64_t>(n, (int64_t)256 * kKsub);
-  std::vector<int64_t> rs(n);
-  std::iota(rs.begin(), rs.end(), 0);
-  if (nr < n) {
-    std::vector<uint64_t> key(n);
-    for (int64_t i = 0; i < n; ++i) key[i] = mix64((prm->seed + 1) * 0x100000001B3ull ^ (uint64_t)i);
-    std::nth_element(rs.begin(), rs.begin() + nr, rs.end(),
-                     [&](int64_t x, int64_t y) { return key[x] < key[y] || (key[x] == key[y] && x < y); });
-    rs.resize(nr);
-    std::sort(rs.begin(), rs.end());
-  }
+  AMP_BHIP(hipStreamSynchronize(st));
+  // residual codebook: k-means per subspace on the sampled residuals, all
+  // subspaces side by side
   std::vector<float> CB((size_t)M * kKsub * dsub);
   {
-    std::vector<float> sub((size_t)nr * dsub), cbm;
-    for (int m = 0; m < M; ++m) {
-      for (int64_t i = 0; i < nr; ++i) {
-        const int64_t r = rs[i];
-        for (int t = 0; t < dsub; ++t)
-          sub[(size_t)i * dsub + t] = base[r * d + m * dsub + t] - C[(size_t)a[r] * d + m * dsub + t];
+    auto resid = [&](int m, int64_t i, float* x) {
+      const int64_t r = rs[i];
+      for (int t = 0; t < dsub; ++t) x[t] = base[r * d + m * dsub + t] - C[(size_t)a[r] * d + m * dsub + t];
+    };
+    std::vector<std::vector<int64_t>> picked(M);
+    parallel_for(M, [&](int64_t m0, int64_t m1, int) {
+      for (int64_t m = m0; m < m1; ++m) {
+        picked[m] = first_distinct(nr, dsub, kKsub, prm->seed + 1000 + m,
+                                   [&](int64_t i, float* x) { resid((int)m, i, x); });
+        for (int c = 0; c < kKsub; ++c) resid((int)m, picked[m][c], &CB[((size_t)m * kKsub + c) * dsub]);
       }
-      if ((s = kmeans(sub.data(), nr, dsub, kKsub, iters, prm->seed + 1000 + m, st, cbm)) != AMP_OK) return s;
+    });
+    std::vector<int32_t> empty;
+    if ((s = kmeans_device(dsmp, nr, dsub, d, M, kKsub, iters, st, CB, empty)) != AMP_OK) return s;
+    std::vector<float> sub, cbm;
+    for (int m = 0; m < M; ++m) {
+      if (!empty[m]) continue;
+      sub.resize((size_t)nr * dsub);
+      for (int64_t i = 0; i < nr; ++i) resid(m, i, &sub[(size_t)i * dsub]);
+      if ((s = kmeans_host(sub, nr, dsub, kKsub, iters, picked[m], st, cbm)) != AMP_OK) return s;
       std::copy(cbm.begin(), cbm.end(), CB.begin() + (size_t)m * kKsub * dsub);
     }
   }
   if (prm->integer_data)
     for (float& v : CB) v = std::nearbyint(v);
-  // encode (residuals on the device, nearest codeword per subspace), and
-  // the largest residual magnitude for the grid step
+  // encode (residuals on the device, nearest codeword of every subspace), the
+  // largest squared residual norm per list and the largest magnitude
   std::vector<uint8_t> codes((size_t)n * M);
+  std::vector<unsigned long long> rad2(nlist, 0);
+  uint32_t amax_bits = 0;
   {
-    Dev dv;
-    float *dX, *dR, *dC, *dCB, *dxn, *dcn;
-    int32_t *da, *dcode;
-    AMP_BHIP(dv.alloc(&dX, (size_t)chunk * d));
-    AMP_BHIP(dv.alloc(&dR, (size_t)chunk * d));
-    AMP_BHIP(dv.alloc(&dC, C.size()));
+    float* dCB;
+    uint8_t* dcode;
+    unsigned long long* drad;
+    uint32_t* dam;
     AMP_BHIP(dv.alloc(&dCB, CB.size()));
-    AMP_BHIP(dv.alloc(&dxn, chunk));
-    AMP_BHIP(dv.alloc(&dcn, kKsub));
-    AMP_BHIP(dv.alloc(&da, chunk));
-    AMP_BHIP(dv.alloc(&dcode, chunk));
-    AMP_BHIP(hipMemcpyAsync(dC, C.data(), C.size() * 4, hipMemcpyHostToDevice, st));
+    AMP_BHIP(dv.alloc(&dcode, (size_t)chunk * M));
+    AMP_BHIP(dv.alloc(&drad, nlist));
+    AMP_BHIP(dv.alloc(&dam, 1));
     AMP_BHIP(hipMemcpyAsync(dCB, CB.data(), CB.size() * 4, hipMemcpyHostToDevice, st));
-    std::vector<int32_t> cm(chunk);
+    AMP_BHIP(hipMemcpyAsync(drad, rad2.data(), (size_t)nlist * 8, hipMemcpyHostToDevice, st));
+    AMP_BHIP(hipMemcpyAsync(dam, &amax_bits, 4, hipMemcpyHostToDevice, st));
+    AMP_BHIP(launch_sqnorm(dCB, (int64_t)M * kKsub, dsub, dcn, st));
     for (int64_t c0 = 0; c0 < n; c0 += chunk) {
       const int64_t m = std::min(chunk, n - c0);
-      AMP_BHIP(hipMemcpyAsync(dX, base + c0 * d, (size_t)m * d * 4, hipMemcpyHostToDevice, st));
-      AMP_BHIP(hipMemcpyAsync(da, a.data() + c0, m * 4, hipMemcpyHostToDevice, st));
-      AMP_BHIP(launch_residual(dX, da, dC, m, d, dR, st));
-      for (int sm = 0; sm < M; ++sm) {
-        AMP_BHIP(launch_assign(dR + sm * dsub, m, dsub, d, dCB + (size_t)sm * kKsub * dsub, kKsub, dxn, dcn, dcode,
-                               nullptr, st));
-        AMP_BHIP(hipMemcpyAsync(cm.data(), dcode, m * 4, hipMemcpyDeviceToHost, st));
-        AMP_BHIP(hipStreamSynchronize(st));
-        for (int64_t i = 0; i < m; ++i) codes[(size_t)(c0 + i) * M + sm] = (uint8_t)cm[i];
+      if (n > chunk) {  // (one chunk: its rows and lists are still on the device)
+        AMP_BHIP(hipMemcpyAsync(dX, base + c0 * d, (size_t)m * d * 4, hipMemcpyHostToDevice, st));
+        AMP_BHIP(hipMemcpyAsync(da, a.data() + c0, m * 4, hipMemcpyHostToDevice, st));
       }
+      AMP_BHIP(launch_residual(dX, da, dC, m, d, dR, st));
+      AMP_BHIP(launch_assign_sub(dR, m, dsub, d, M, dCB, dcn, nullptr, dcode, st));
+      AMP_BHIP(launch_radius(dX, dR, da, m, d, prm->metric == AMP_IP, drad, dam, st));
+      AMP_BHIP(hipMemcpyAsync(codes.data() + (size_t)c0 * M, dcode, (size_t)m * M, hipMemcpyDeviceToHost, st));
     }
+    AMP_BHIP(hipMemcpyAsync(rad2.data(), drad, (size_t)nlist * 8, hipMemcpyDeviceToHost, st));
+    AMP_BHIP(hipMemcpyAsync(&amax_bits, dam, 4, hipMemcpyDeviceToHost, st));
+    AMP_BHIP(hipStreamSynchronize(st));
   }
   // list layout: by list, ids increasing inside a list
   std::vector<int64_t> idv(n);
@@ -349,32 +441,22 @@ static amp_status amp_index_build_body(const void* base_in, int64_t n, int32_t d
   });
   std::vector<int64_t> sid(n);
   std::vector<uint8_t> scodes((size_t)n * M);
-  for (int64_t j = 0; j < n; ++j) {
-    sid[j] = idv[order[j]];
-    std::memcpy(&scodes[(size_t)j * M], &codes[(size_t)order[j] * M], M);
-  }
-  // radius (FP64) and the largest residual magnitude, per thread then merged
-  const int T = n_threads();
-  std::vector<std::vector<double>> radt(T, std::vector<double>(nlist, 0.0));
-  std::vector<double> amax(T, 0.0);
-  parallel_for(n, [&](int64_t i0, int64_t i1, int t) {
-    for (int64_t i = i0; i < i1; ++i) {
-      double s2 = 0.0;
-      for (int u = 0; u < d; ++u) {
-        const double r = (double)(base[i * d + u] - C[(size_t)a[i] * d + u]);  // FP32 residual
-        s2 += r * r;
-        amax[t] = std::max(amax[t], std::fabs(r));
-        if (prm->metric == AMP_IP) amax[t] = std::max(amax[t], (double)std::fabs(base[i * d + u]));
-      }
-      radt[t][a[i]] = std::max(radt[t][a[i]], std::sqrt(s2));
+  parallel_for(n, [&](int64_t j0, int64_t j1, int) {
+    for (int64_t j = j0; j < j1; ++j) {
+      sid[j] = idv[order[j]];
+      std::memcpy(&scodes[(size_t)j * M], &codes[(size_t)order[j] * M], M);
     }
   });
+  // radius (FP64) and the largest magnitude
   std::vector<double> rad(nlist, 0.0);
-  double A = 0.0;
-  for (int t = 0; t < T; ++t) {
-    A = std::max(A, amax[t]);
-    for (int p = 0; p < nlist; ++p) rad[p] = std::max(rad[p], radt[t][p]);
+  for (int p = 0; p < nlist; ++p) {
+    double v;
+    std::memcpy(&v, &rad2[p], 8);
+    rad[p] = std::sqrt(v);
   }
+  float amax;
+  std::memcpy(&amax, &amax_bits, 4);
+  double A = amax;
   for (float v : CB) A = std::max(A, (double)std::fabs(v));
   if (prm->metric == AMP_IP)
     for (float v : C) A = std::max(A, (double)std::fabs(v));

@@ -10,6 +10,7 @@
 //                        per-pair quantisation, packed-lane DC scan, pruning
 //                        against the query's running threshold (TSM forwarding)
 //   k_merge              TS: per-query top-k by (distance, id)
+#include "build_kernels.h"
 #include "scan_kernels.h"
 
 #include <cstdio>
@@ -2091,6 +2092,12 @@ hipError_t launch_assign(const float* X, int64_t n, int dd, int ld, const float*
   hipLaunchKernelGGL(k_sqnorm_ld, dim3((unsigned)((k + 3) / 4)), dim3(256), 0, st, C, (int64_t)k, dd, dd, cn);
   hipLaunchKernelGGL(k_assign, dim3((unsigned)((n + CL_T - 1) / CL_T)), dim3(256), 0, st, X, xn, n, dd, ld, C, cn, k,
                      out_a, out_d);
+  return hipGetLastError();
+}
+
+hipError_t launch_sqnorm(const float* X, int64_t n, int dd, float* out, hipStream_t st) {
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_sqnorm_ld, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, st, X, n, dd, dd, out);
   return hipGetLastError();
 }
 
