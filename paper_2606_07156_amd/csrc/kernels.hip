@@ -16,54 +16,90 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 
 namespace amp {
 
-// ------------------------------------------------------------------ resets
-// the per-search resets of the search workspace in one launch (fills by
-// kernel, not memsets: a captured search graph holds no memset node):
-// bucket counters, unit counters, flags and work counters to 0, bounds to
-// "none", candidate counts to 0
-struct ResetArgs {
-  uint32_t* cnt;
+// ------------------------------------------------------------------ front
+// The first launch of a search: the per-search resets of the workspace (fills
+// by kernel, not memsets: a captured search graph holds no memset node), the
+// per-query sizes handed over in device memory, and one pass over the query
+// rows that widens BF16 rows, takes their squared norms and puts them on the
+// operand grid, as far as the search needs each.  (Separate launches took 5 us
+// each, 30 us of a 4096 x 768 BF16 batch in all: 12 us now.)
+struct FrontArgs {
+  uint32_t* cnt;     // bucket counters -> 0
   size_t ncnt;
-  uint32_t* counters;
+  uint32_t* counters;  // unit counters -> 0
   size_t ncounters;
-  uint32_t* flags;   // [4]
-  uint64_t* work;    // [4]
-  uint64_t* tau;     // [nq]
-  uint32_t* ccount;  // [nq]
-  int32_t* ipmask;   // [nq] or null
-  size_t nq;
+  uint32_t* flags;   // [4] -> 0
+  uint64_t* work;    // [4] -> 0
+  uint64_t* tau;     // [nq] -> no bound
+  uint32_t* ccount;  // [nq] -> 0
+  int32_t* ipmask;   // [nq] -> 0, or null
+  const int32_t* kin;   // device sizes, or null: each k into [1, kmax] and
+  const int32_t* npin;  // nprobe into [1, npmax] (flag 32 if one was outside)
+  int32_t* kout;
+  int32_t* npout;
+  int kmax, npmax;
+  const float* q;        // FP32 rows, or
+  const uint16_t* qb;    // BF16 rows, widened (exact) into qw
+  float* qw;
+  float* qn;             // [nq] squared norms, or null
+  int16_t* qi;           // [nq][d] rows on the grid, or null
+  int rows;              // 1: any of qw, qn, qi is wanted
+  int nq, d, grid_e, grid_kind;
 };
-__global__ void k_reset(ResetArgs r) {
+__device__ __forceinline__ void clamp_sizes(const FrontArgs& a, int i) {
+  const int kv = a.kin[i], nv = a.npin[i];
+  const int kc = kv < 1 ? 1 : (kv > a.kmax ? a.kmax : kv);
+  const int nc = nv < 1 ? 1 : (nv > a.npmax ? a.npmax : nv);
+  if (kc != kv || nc != nv) atomicOr(&a.flags[0], 32u);
+  a.kout[i] = kc;
+  a.npout[i] = nc;
+}
+// queries whose sizes workgroup 0 clamps itself (it has reset the flags they
+// may raise); more of them take a launch of their own
+constexpr int kFrontSizes = 8192;
+__global__ __launch_bounds__(256) void k_front(FrontArgs a) {
   const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x, st = (size_t)gridDim.x * blockDim.x;
-  for (size_t i = i0; i < r.ncnt; i += st) r.cnt[i] = 0;
-  for (size_t i = i0; i < r.ncounters; i += st) r.counters[i] = 0;
-  for (size_t i = i0; i < r.nq; i += st) {
-    r.tau[i] = ~0ull;
-    r.ccount[i] = 0;
-    if (r.ipmask) r.ipmask[i] = 0;
-  }
   if (i0 < 4) {
-    r.flags[i0] = 0;
-    r.work[i0] = 0;
+    a.flags[i0] = 0;
+    a.work[i0] = 0;
+  }
+  if (blockIdx.x == 0 && a.kin && a.nq <= kFrontSizes) {
+    __threadfence();  // the flags are zero before any thread raises one
+    __syncthreads();
+#pragma unroll 4
+    for (int i = threadIdx.x; i < a.nq; i += 256) clamp_sizes(a, i);
+  }
+  for (size_t i = i0; i < a.ncnt; i += st) a.cnt[i] = 0;
+  for (size_t i = i0; i < a.ncounters; i += st) a.counters[i] = 0;
+  for (size_t i = i0; i < (size_t)a.nq; i += st) {
+    a.tau[i] = ~0ull;
+    a.ccount[i] = 0;
+    if (a.ipmask) a.ipmask[i] = 0;
+  }
+  if (!a.rows) return;
+  const int lane = threadIdx.x & 63;
+  for (int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); r < a.nq; r += (int64_t)gridDim.x * 4) {
+    const size_t o = (size_t)r * a.d;
+    float s = 0.f;  // lane-strided partial sums, then a butterfly: k_sqnorm's order
+    for (int t = lane; t < a.d; t += 64) {
+      const float x = a.qb ? __uint_as_float((uint32_t)a.qb[o + t] << 16) : a.q[o + t];
+      if (a.qb) a.qw[o + t] = x;
+      if (a.qi) a.qi[o + t] = (int16_t)grid_val(x, a.grid_e, a.grid_kind);
+      s = fmaf(x, x, s);
+    }
+    if (a.qn) {
+      for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+      if (lane == 0) a.qn[r] = s;
+    }
   }
 }
-
-// per-query sizes handed over in device memory: each k into [1, kmax] and
-// nprobe into [1, npmax] (flag 32 if one was outside), copied into the
-// workspace's per-query arrays
-__global__ void k_sizes(const int32_t* __restrict__ kin, const int32_t* __restrict__ npin, int32_t* __restrict__ kout,
-                        int32_t* __restrict__ npout, int nq, int kmax, int npmax, int32_t* flags) {
+__global__ void k_sizes(FrontArgs a) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nq) return;
-  const int kv = kin[i], nv = npin[i];
-  const int kc = kv < 1 ? 1 : (kv > kmax ? kmax : kv);
-  const int nc = nv < 1 ? 1 : (nv > npmax ? npmax : nv);
-  if (kc != kv || nc != nv) atomicOr(&flags[0], 32);
-  kout[i] = kc;
-  npout[i] = nc;
+  if (i < a.nq) clamp_sizes(a, i);
 }
 
 // status word of a search from its error flags (the host-mode mapping):
@@ -209,12 +245,6 @@ __global__ void k_prep_cbi(const float* __restrict__ cb, int M, int dsub, int gr
   if (i >= M * kKsub * 8) return;
   const int t = i & 7, e = i >> 3;
   cbi[i] = t < dsub ? (int16_t)grid_val(cb[(size_t)e * dsub + t], grid_e, grid_kind) : (int16_t)0;
-}
-
-// bfloat16 bit patterns to FP32 (exact: the pattern is the top half)
-__global__ void k_bf16_widen(const uint16_t* __restrict__ in, float* __restrict__ out, size_t n) {
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-    out[i] = __uint_as_float((uint32_t)in[i] << 16);
 }
 
 // ------------------------------------------------------------------ index build
@@ -868,6 +898,7 @@ struct QueueArgs {
                           // joins phase 2
   int fkeys;              // pbase holds FP32 keys (FP32 policy)
   const uint64_t* tau;    // the queries' phase-1 bounds (with pbase)
+  int all_offsets;        // k_queue_small: every bucket's offsets are wanted (statistics)
   uint64_t* work;         // phase-2 work counters (pairs dropped here count as skipped), or null
 };
 
@@ -946,68 +977,96 @@ __global__ void k_qtot(QueueArgs a, int fp32) {
 #pragma unroll
   for (int u = 0; u < kQSub; ++u) cnt[(size_t)u * NB + b] = x[u];
   const int64_t n = a.offsets[p + 1] - a.offsets[p];
-  const int64_t nch = (n + a.chunk[ph] - 1) / a.chunk[ph];
+  const int64_t ck0 = a.chunk[0], ck = ph ? a.chunk[1] : ck0;
+  const int64_t nch = (n + ck - 1) / ck;
   const int G = class_pairs(cls, a.wpr, fp32, a.gran, a.M);
   const int pos = cls * a.nlist + a.lpos[p];
   a.pairoff[(size_t)ph * (NB + 1) + pos] = c;
   a.unitoff[(size_t)ph * (NB + 1) + pos] = ((c + G - 1) / G) * nch;
 }
 
-// inclusive scan of one int64 over a 1024-thread workgroup (wave scans, then
-// a scan of the 16 wave totals)
-__device__ __forceinline__ int64_t block_scan_1024(int64_t v, int64_t* s_w) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int64_t o = __shfl_up(v, off);
-    if (lane >= off) v += o;
-  }
-  if (lane == 63) s_w[wv] = v;
-  __syncthreads();
-  if (wv == 0) {
-    int64_t t = lane < 16 ? s_w[lane] : 0;
-#pragma unroll
-    for (int off = 1; off < 16; off <<= 1) {
-      const int64_t o = __shfl_up(t, off);
-      if (lane >= off) t += o;
-    }
-    if (lane < 16) s_w[lane] = t;
-  }
-  __syncthreads();
-  const int64_t r = v + (wv ? s_w[wv - 1] : 0);
-  __syncthreads();  // s_w is reused by the next scan
-  return r;
+// inclusive sum over the wave's lanes (row shifts, then row broadcasts: no LDS
+// permutes, whose latency is most of a scan in a one-workgroup kernel)
+__device__ __forceinline__ uint32_t wave_sum_scan(uint32_t v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);  // row_shr:1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15 into rows 1, 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31 into rows 2, 3
+  return v;
 }
-
-// exclusive scans of the pair and unit counts in launch order, one
-// workgroup of 1024 threads, each a contiguous run of positions
-__global__ __launch_bounds__(1024) void k_qscan(QueueArgs a, int fp32) {
-  __shared__ int64_t s_w[16];
-  const int NB = a.ncls * a.nlist;
-  const int per = (NB + 1023) / 1024;
-  for (int ph = a.ph0; ph < a.ph1; ++ph) {
-    int64_t* po = a.pairoff + (size_t)ph * (NB + 1);
-    int64_t* uo = a.unitoff + (size_t)ph * (NB + 1);
-    const int b0 = threadIdx.x * per;
-    int64_t sp = 0, su = 0;
-    for (int b = b0; b < b0 + per && b < NB; ++b) {
-      sp += po[b];
-      su += uo[b];
-    }
-    const int64_t ip = block_scan_1024(sp, s_w), iu = block_scan_1024(su, s_w);
-    int64_t xp = ip - sp, xu = iu - su;  // exclusive
-    if (threadIdx.x == 1023) {
-      po[NB] = ip;
-      uo[NB] = iu;
-    }
-    for (int b = b0; b < b0 + per && b < NB; ++b) {
-      const int64_t cp = po[b], cu = uo[b];
-      po[b] = xp;
-      uo[b] = xu;
-      xp += cp;
-      xu += cu;
-    }
+// exclusive sums of two counts over a workgroup of up to 1024 threads; s_w:
+// 16 pairs of words of LDS, free again on return
+__device__ __forceinline__ uint2 block_exclusive2(uint32_t a, uint32_t b, uint2* s_w, uint2* total) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const uint32_t ia = wave_sum_scan(a), ib = wave_sum_scan(b);
+  if (threadIdx.x < 16) s_w[threadIdx.x] = make_uint2(0, 0);
+  __syncthreads();
+  if (lane == 63) s_w[wv] = make_uint2(ia, ib);
+  __syncthreads();
+  uint2 below = make_uint2(0, 0), all = make_uint2(0, 0);
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    const uint2 t = s_w[w];
+    if (w < wv) below = make_uint2(below.x + t.x, below.y + t.y);
+    all = make_uint2(all.x + t.x, all.y + t.y);
   }
+  __syncthreads();
+  *total = all;
+  return make_uint2(below.x + ia - a, below.y + ib - b);
+}
+// buckets of a thread's run (odd: the runs start in distinct LDS banks)
+__host__ __device__ __forceinline__ int bucket_run(int NB, int threads) { return ((NB + threads - 1) / threads) | 1; }
+
+// exclusive scans of the pair and unit counts in launch order, one workgroup
+// of 1024 threads: the counts come in coalesced and are scanned in LDS, each
+// thread a contiguous run.  (Runs read straight from memory took a cache line
+// per lane: 35 us for 12288 buckets, 13 this way.)  A bucket's units are held
+// in 32 bits, saturated: beyond any unit table.
+__global__ __launch_bounds__(1024) void k_qscan(QueueArgs a, int fp32) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  uint32_t* v = reinterpret_cast<uint32_t*>(lds);  // [NB]
+  __shared__ int64_t s_base[1024], s_w[16];
+  const int NB = a.ncls * a.nlist, tid = threadIdx.x;
+  const int per = bucket_run(NB, 1024), b0 = tid * per, b1 = b0 + per < NB ? b0 + per : NB;
+  for (int ph = a.ph0; ph < a.ph1; ++ph)
+    for (int t = 0; t < 2; ++t) {
+      int64_t* arr = (t ? a.unitoff : a.pairoff) + (size_t)ph * (NB + 1);
+#pragma unroll 4
+      for (int b = tid; b < NB; b += 1024) {
+        const int64_t c = arr[b];
+        v[b] = c < 0xFFFFFFFFll ? (uint32_t)c : 0xFFFFFFFFu;
+      }
+      __syncthreads();
+      int64_t sum = 0;
+      for (int b = b0; b < b1; ++b) {
+        const uint32_t c = v[b];
+        v[b] = (uint32_t)sum;  // offset inside the run (a run that overflows it has overflowed any table)
+        sum += c;
+      }
+      // 64-bit sums of the runs: wave scans, then the sixteen wave totals
+      const int lane = tid & 63, wv = tid >> 6;
+      int64_t inc = sum;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int64_t x = __shfl_up(inc, o);
+        if (lane >= o) inc += x;
+      }
+      if (lane == 63) s_w[wv] = inc;
+      __syncthreads();
+      int64_t below = 0, total = 0;
+#pragma unroll
+      for (int w = 0; w < 16; ++w) {
+        if (w < wv) below += s_w[w];
+        total += s_w[w];
+      }
+      s_base[tid] = below + inc - sum;
+      __syncthreads();
+      for (int b = tid; b < NB; b += 1024) arr[b] = s_base[b / per] + v[b];
+      if (tid == 0) arr[NB] = total;
+      __syncthreads();  // the LDS is filled again
+    }
 }
 
 __global__ void k_qscatter(QueueArgs a) {
@@ -1047,12 +1106,149 @@ __global__ void k_qunits(QueueArgs a, int fp32) {
       }
       const int b = lo, cls = b / a.nlist, p = a.lorder[b % a.nlist];
       const int64_t n = a.offsets[p + 1] - a.offsets[p];
-      const int64_t nch = (n + a.chunk[ph] - 1) / a.chunk[ph];
+      const int64_t ck0 = a.chunk[0], ck = ph ? a.chunk[1] : ck0;
+      const int64_t nch = (n + ck - 1) / ck;
       const int G = class_pairs(cls, a.wpr, fp32, a.gran, a.M);
       const int64_t local = u - uo[b], grp = local / nch, ch = local % nch;
       const int64_t left = (po[b + 1] - po[b]) - grp * G;
       units[u] = make_int4(p, (int)(po[b] + grp * G), (int)(left < G ? left : G), (int)ch);
     }
+  }
+}
+
+// The whole queue build of a small batch (at most kSmallQueue pairs) in one
+// workgroup: U pairs per thread in registers, list lengths, bucket counts and
+// offsets in LDS; the first pair of a unit writes it.  The five launches above
+// are latency and launch gaps there (each 2 to 5 us for one query, 42 us per
+// search for the two builds; 11 us this way).  What remains is two dependent
+// reads of fresh data (the pairs, then their lists): all of a thread's pairs
+// are read before any is used.  Whole searches with five launches / with one:
+// 132 / 106 us for 512 pairs over 1024 lists, 140 / 116 for 2048, 166 / 148 for
+// 4096, 172 / 175 for 8192; over 4096 lists 222 / 179 us for 512 pairs, 379 /
+// 389 for 8192.
+constexpr int kSmallQueue = 4096;
+constexpr int kSmallBuckets = 15360;  // eight bytes of LDS each, beside four per pair
+template <int U>
+__global__ __launch_bounds__(1024) void k_queue_small(QueueArgs a, int fp32) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  const int tid = threadIdx.x, nt = blockDim.x, NB = a.ncls * a.nlist, n = a.nq * a.npmax;
+  uint32_t* cnt = reinterpret_cast<uint32_t*>(lds);  // [NB] pairs, then with their offset << 14
+  uint32_t* off = cnt + NB;                          // [NB] list chunks, then the unit offset
+  uint32_t* len = off + NB;                          // [n] list lengths
+  __shared__ uint2 s_w[16];
+  const int per = bucket_run(NB, nt), b0 = tid * per, b1 = b0 + per < NB ? b0 + per : NB;
+  // pairs of a unit by class: powers of two
+  const int g0 = __builtin_ctz(class_pairs(0, a.wpr, fp32, a.gran, a.M));
+  const int g1 = __builtin_ctz(class_pairs(1, a.wpr, fp32, a.gran, a.M));
+  const int g2 = __builtin_ctz(class_pairs(2, a.wpr, fp32, a.gran, a.M));
+  const int nl = a.nlist, lgs = g0 | g1 << 8 | g2 << 16;
+  auto lg_pairs = [nl, lgs](int b) { return lgs >> (8 * ((b >= nl) + (b >= 2 * nl))) & 255; };
+  // (lists are shorter than 2^31, so a longer chunk is one)
+  const uint32_t ck0 = a.chunk[0] < (1ll << 31) ? (uint32_t)a.chunk[0] : 1u << 31;
+  const uint32_t ck1 = a.chunk[1] < (1ll << 31) ? (uint32_t)a.chunk[1] : 1u << 31;
+  int p[U], cls[U], kk[U];
+  int64_t key[U];
+  uint64_t tau[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int i = tid + u * nt, j = i < n ? i : 0;
+    p[u] = i < n ? a.probes[j] : -1;
+    cls[u] = a.pbits[j];
+    key[u] = a.pbase ? a.pbase[j] : 0;
+    tau[u] = a.pbase ? a.tau[j / a.npmax] : 0;
+    kk[u] = a.ph0 == 0 ? (a.kq ? a.kq[j / a.npmax] : a.kconst) : 0;
+  }
+  uint32_t ln[U];
+  int lp[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int l = p[u] < 0 ? 0 : p[u];
+    ln[u] = (uint32_t)(a.offsets[l + 1] - a.offsets[l]);
+    lp[u] = a.lpos[l];
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int i = tid + u * nt;
+    if (i < n) len[i] = ln[u];
+    cls[u] = p[u] < 0 ? 0 : pair_class(cls[u], a.M, a.gran);
+  }
+  for (int ph = a.ph0; ph < a.ph1; ++ph) {
+    const uint32_t ch = ph ? ck1 : ck0;
+    for (int b = tid; b < NB; b += nt) cnt[b] = 0;
+    int rank[U];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = tid + u * nt;
+      rank[u] = -1;
+      if (p[u] < 0) continue;
+      bool in;
+      if (ph == 0) {  // in_phase1: the lists of the ranks before hold fewer than k vectors
+        const int r = i % a.npmax;
+        int64_t cum = 0;
+        in = true;
+        for (int j = i - r; j < i && in; ++j) {
+          cum += len[j];
+          in = cum < kk[u];
+        }
+      } else {
+        in = !a.pbase || (a.fkeys ? (uint64_t)key[u] : ikey(key[u])) <= tau[u];
+        if (!in && a.work) atomicAdd((unsigned long long*)&a.work[2], 1ull);
+      }
+      if (!in) continue;
+      const int b = cls[u] * a.nlist + lp[u];
+      rank[u] = (int)atomicAdd(&cnt[b], 1u);
+      off[b] = (ln[u] + ch - 1) / ch;  // (the same for every pair of the bucket)
+    }
+    __syncthreads();
+    // exclusive scans of pairs and units in launch order, a run per thread
+    uint32_t sp = 0, su = 0;
+    for (int b = b0; b < b1; ++b) {
+      const uint32_t c = cnt[b], nc = off[b];  // (nc: garbage in an empty bucket)
+      const int lg = lg_pairs(b);
+      sp += c;
+      su += c ? ((c + (1u << lg) - 1) >> lg) * nc : 0;
+    }
+    uint2 tot;
+    const uint2 ex = block_exclusive2(sp, su, s_w, &tot);
+    uint32_t xp = ex.x, xu = ex.y;
+    int64_t* po = a.pairoff + (size_t)ph * (NB + 1);
+    int64_t* uo = a.unitoff + (size_t)ph * (NB + 1);
+    for (int b = b0; b < b1; ++b) {
+      const uint32_t c = cnt[b], nc = off[b];
+      const int lg = lg_pairs(b);
+      // (the scan kernels read the class boundaries only; all of them on request)
+      if (a.all_offsets || b == 0 || b == a.nlist || b == 2 * a.nlist) {
+        po[b] = xp;
+        uo[b] = xu;
+      }
+      cnt[b] = c | xp << 14;
+      off[b] = xu;
+      xp += c;
+      xu += c ? ((c + (1u << lg) - 1) >> lg) * nc : 0;
+    }
+    const bool fits = (int64_t)tot.y <= a.max_units;
+    if (tid == 0) {
+      po[NB] = tot.x;
+      uo[NB] = tot.y;
+      if (!fits) atomicOr(&a.flags[0], 4);
+    }
+    __syncthreads();
+    int4* units = a.units + (size_t)ph * a.max_units;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int r = rank[u];
+      if (r < 0) continue;
+      const int b = cls[u] * a.nlist + lp[u];
+      const int c = (int)(cnt[b] & 16383u), first = (int)(cnt[b] >> 14), lg = lg_pairs(b);
+      a.sorted[(size_t)ph * n + first + r] = tid + u * nt;
+      if (fits && (r & ((1 << lg) - 1)) == 0) {
+        const int nc = (int)((ln[u] + ch - 1) / ch), left = c - r < 1 << lg ? c - r : 1 << lg;
+        int4* w = units + off[b] + (size_t)(r >> lg) * nc;
+        for (int k = 0; k < nc; ++k) w[k] = make_int4(p[u], first + r, left, k);
+      }
+    }
+    __syncthreads();  // the counts are cleared for the next phase
   }
 }
 
@@ -1063,6 +1259,22 @@ __global__ void k_qunits(QueueArgs a, int fp32) {
 // buffer is emptied for phase 2.  Queries with at most 64 entries: one wave
 // each (register bitonic sort); the rest: k_tau, a workgroup each (radix
 // select).
+__device__ __forceinline__ void tau_wave(uint32_t* ccount, const uint64_t* ckey, uint64_t* tau, int q, int n, int kk,
+                                         size_t capq) {
+  const int lane = threadIdx.x & 63;
+  uint64_t key = lane < n ? ckey[(size_t)q * capq + lane] : ~0ull;
+  for (int kb = 2; kb <= 64; kb <<= 1)
+    for (int jb = kb >> 1; jb > 0; jb >>= 1) {
+      const uint64_t o = __shfl_xor(key, jb);
+      const bool keep_min = ((lane & kb) == 0) == ((lane & jb) == 0);
+      key = keep_min ? (o < key ? o : key) : (o > key ? o : key);
+    }
+  const uint64_t kth = __shfl(key, kk <= 64 ? kk - 1 : 63);
+  if (lane == 0) {
+    tau[q] = n >= kk ? kth : ~0ull;
+    ccount[q] = 0;
+  }
+}
 __global__ __launch_bounds__(256) void k_tau_wave(uint32_t* ccount, const uint64_t* ckey, uint64_t* tau,
                                                   const int32_t* kq, int kconst, int nq, size_t capq,
                                                   int32_t* nrerun) {
@@ -1073,21 +1285,8 @@ __global__ __launch_bounds__(256) void k_tau_wave(uint32_t* ccount, const uint64
   const uint32_t cnt = ccount[q];
   const int n = (int)(cnt < capq ? cnt : capq);
   if (n > 64) return;
-  uint64_t key = lane < n ? ckey[(size_t)q * capq + lane] : ~0ull;
-  for (int kb = 2; kb <= 64; kb <<= 1)
-    for (int jb = kb >> 1; jb > 0; jb >>= 1) {
-      const uint64_t o = __shfl_xor(key, jb);
-      const bool keep_min = ((lane & kb) == 0) == ((lane & jb) == 0);
-      key = keep_min ? (o < key ? o : key) : (o > key ? o : key);
-    }
-  const int kk = kq ? kq[q] : kconst;
-  const uint64_t kth = __shfl(key, kk <= 64 ? kk - 1 : 63);
-  if (lane == 0) {
-    tau[q] = n >= kk ? kth : ~0ull;
-    ccount[q] = 0;
-  }
+  tau_wave(ccount, ckey, tau, q, n, kq ? kq[q] : kconst, capq);
 }
-
 __global__ __launch_bounds__(256) void k_tau(uint32_t* ccount, const uint64_t* ckey, uint64_t* tau,
                                              const int32_t* kq, int kconst, int nq, size_t capq) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -1133,6 +1332,38 @@ __global__ __launch_bounds__(256) void k_tau(uint32_t* ccount, const uint64_t* c
       // (the select ends on a barrier: the LDS is free for the next query)
     }
     __syncthreads();  // every thread has read the list before it is reset
+  }
+}
+
+// both of them for a small batch (at most kSmallBatch queries), a workgroup
+// per query (with the merge kernels fused the same way, whole searches 122.5 ->
+// 114.7 us for 64 queries, 564 -> 550 for 512 of k 100; even at 1024, slower
+// beyond)
+constexpr int kSmallBatch = 512;
+__global__ __launch_bounds__(256) void k_tau_small(uint32_t* ccount, const uint64_t* ckey, uint64_t* tau,
+                                                   const int32_t* kq, int kconst, size_t capq, int32_t* nrerun) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  uint64_t* keys = reinterpret_cast<uint64_t*>(lds);
+  uint32_t* hist = reinterpret_cast<uint32_t*>(lds + capq * 8);  // [256]
+  uint32_t* sel = hist + 256;                                     // [2]
+  const int q = blockIdx.x;
+  if (q == 0 && threadIdx.x < 2) nrerun[threadIdx.x] = 0;
+  const uint32_t cnt = ccount[q];
+  const int n = (int)(cnt < capq ? cnt : capq), kk = kq ? kq[q] : kconst;
+  __syncthreads();  // every thread has read the count before it is reset
+  if (n <= 64) {
+    if (threadIdx.x < 64) tau_wave(ccount, ckey, tau, q, n, kk, capq);
+    return;
+  }
+  uint64_t kth = ~0ull;
+  if (n >= kk) {  // uniform over the workgroup
+    for (int i = threadIdx.x; i < n; i += blockDim.x) keys[i] = ckey[(size_t)q * capq + i];
+    __syncthreads();
+    kth = block_select_u64(keys, n, kk, hist, sel);
+  }
+  if (threadIdx.x == 0) {
+    tau[q] = kth;
+    ccount[q] = 0;
   }
 }
 
@@ -1262,14 +1493,8 @@ __device__ __forceinline__ void merge_emit(const MergeArgs& a, int q, int r, int
 
 // queries with at most 64 candidates: one wave per query, a register bitonic
 // sort of (key, id) across the lanes
-__global__ __launch_bounds__(256) void k_merge_wave(MergeArgs a, int nq) {
+__device__ __forceinline__ void merge_wave(const MergeArgs& a, int q, int n, int kk) {
   const int lane = threadIdx.x & 63;
-  const int q = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (q >= nq) return;
-  const uint32_t cnt = a.ccount[q];
-  if (cnt > a.capq && lane == 0) atomicOr(&a.flags[0], 2);
-  const int n = (int)(cnt < a.capq ? cnt : a.capq);
-  if (n > 64) return;  // the workgroup kernel takes it
   uint64_t key = lane < n ? a.ckey[(size_t)q * a.capq + lane] : ~0ull;
   int64_t id = lane < n ? a.cid[(size_t)q * a.capq + lane] : INT64_MAX;
   for (int kb = 2; kb <= 64; kb <<= 1)
@@ -1284,8 +1509,16 @@ __global__ __launch_bounds__(256) void k_merge_wave(MergeArgs a, int nq) {
         id = oid;
       }
     }
-  const int kk = a.kq ? a.kq[q] : a.kconst;
   for (int r = lane; r < a.kmax; r += 64) merge_emit(a, q, r, n, kk, key, id);
+}
+__global__ __launch_bounds__(256) void k_merge_wave(MergeArgs a, int nq) {
+  const int q = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (q >= nq) return;
+  const uint32_t cnt = a.ccount[q];
+  if (cnt > a.capq && (threadIdx.x & 63) == 0) atomicOr(&a.flags[0], 2);
+  const int n = (int)(cnt < a.capq ? cnt : a.capq);
+  if (n > 64) return;  // the workgroup kernel takes it
+  merge_wave(a, q, n, a.kq ? a.kq[q] : a.kconst);
 }
 
 // queries with more than 64 candidates and more than k: a workgroup per
@@ -1295,9 +1528,11 @@ __global__ __launch_bounds__(256) void k_merge_wave(MergeArgs a, int nq) {
 // queries (at most k candidates, or more than kMergeSel up to the k-th key)
 // are left to k_merge_full, marked by id -2 in their first output row.
 constexpr int kMergeSel = 256;
+inline size_t merge_select_lds(size_t capq) { return capq * 8 + kMergeSel * 20 + 4 * (256 + 3); }
 
-__global__ __launch_bounds__(256) void k_merge(MergeArgs a, int nq) {
-  extern __shared__ __attribute__((aligned(16))) char lds[];
+// by selection; false (nothing written) with more than kMergeSel candidates
+// up to the k-th key.  Ends with the LDS free.
+__device__ __forceinline__ bool merge_select(const MergeArgs& a, int q, int n, int kk, char* lds) {
   uint64_t* keys = reinterpret_cast<uint64_t*>(lds);
   uint64_t* skey = reinterpret_cast<uint64_t*>(lds + a.capq * 8);  // [kMergeSel]
   int64_t* sval = reinterpret_cast<int64_t*>(skey + kMergeSel);    // [kMergeSel]
@@ -1305,76 +1540,97 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a, int nq) {
   uint32_t* hist = reinterpret_cast<uint32_t*>(sidx + kMergeSel);  // [256]
   uint32_t* sel = hist + 256;                                       // [2]
   uint32_t* s_cnt = sel + 2;
+  for (int i = threadIdx.x; i < n; i += blockDim.x) keys[i] = a.ckey[(size_t)q * a.capq + i];
+  if (threadIdx.x == 0) *s_cnt = 0;
+  __syncthreads();
+  const uint64_t v = block_select_u64(keys, n, kk, hist, sel);
+  for (int i = threadIdx.x; i < n; i += blockDim.x)
+    if (keys[i] <= v) {
+      const uint32_t j = atomicAdd(s_cnt, 1u);
+      if (j < (uint32_t)kMergeSel) {
+        skey[j] = keys[i];
+        sval[j] = a.cid[(size_t)q * a.capq + i];
+        sidx[j] = i;
+      }
+    }
+  __syncthreads();
+  const int ns = (int)*s_cnt;
+  if (ns <= kMergeSel) {
+    for (int t = threadIdx.x; t < ns; t += blockDim.x) {
+      const uint64_t kt = skey[t];
+      const int64_t it = sval[t];
+      const int xt = sidx[t];
+      int rank = 0;
+      for (int j = 0; j < ns; ++j) {
+        const uint64_t kj = skey[j];
+        const int64_t ij = sval[j];
+        rank += kj < kt || (kj == kt && (ij < it || (ij == it && sidx[j] < xt)));
+      }
+      if (rank < kk) merge_emit(a, q, rank, n, kk, kt, it);
+    }
+    for (int r = kk + threadIdx.x; r < a.kmax; r += blockDim.x) merge_emit(a, q, r, n, kk, ~0ull, INT64_MAX);
+  }
+  __syncthreads();
+  return ns <= kMergeSel;
+}
+
+// by a sort of every candidate by (key, id) in LDS (bitonic over the next
+// power of two).  Ends with the LDS free.
+__device__ __forceinline__ void merge_sort(const MergeArgs& a, int q, int n, int kk, char* lds) {
+  uint64_t* keys = reinterpret_cast<uint64_t*>(lds);
+  int64_t* vals = reinterpret_cast<int64_t*>(lds + a.capq * 8);
+  int np2 = 1;
+  while (np2 < n) np2 <<= 1;
+  for (int i = threadIdx.x; i < np2; i += blockDim.x) {
+    keys[i] = i < n ? a.ckey[(size_t)q * a.capq + i] : ~0ull;
+    vals[i] = i < n ? a.cid[(size_t)q * a.capq + i] : INT64_MAX;
+  }
+  __syncthreads();
+  block_bitonic_u64_i64(keys, vals, np2);
+  for (int r = threadIdx.x; r < a.kmax; r += blockDim.x)
+    merge_emit(a, q, r, n, kk, r < n ? keys[r] : ~0ull, r < n ? vals[r] : INT64_MAX);
+  __syncthreads();
+}
+
+__global__ __launch_bounds__(256) void k_merge(MergeArgs a, int nq) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
   for (int q = blockIdx.x; q < nq; q += gridDim.x) {
     const uint32_t cnt = a.ccount[q];
     if (cnt > a.capq && threadIdx.x == 0) atomicOr(&a.flags[0], 2);
     const int n = (int)(cnt < a.capq ? cnt : a.capq);
     if (n <= 64) continue;  // uniform over the workgroup
     const int kk = a.kq ? a.kq[q] : a.kconst;
-    if (kk >= n) {
+    if (kk >= n || !merge_select(a, q, n, kk, lds)) {
       if (threadIdx.x == 0) a.out_ids[(size_t)q * a.kmax] = -2;
-      continue;
     }
-    for (int i = threadIdx.x; i < n; i += blockDim.x) keys[i] = a.ckey[(size_t)q * a.capq + i];
-    if (threadIdx.x == 0) *s_cnt = 0;
-    __syncthreads();
-    const uint64_t v = block_select_u64(keys, n, kk, hist, sel);
-    for (int i = threadIdx.x; i < n; i += blockDim.x)
-      if (keys[i] <= v) {
-        const uint32_t j = atomicAdd(s_cnt, 1u);
-        if (j < (uint32_t)kMergeSel) {
-          skey[j] = keys[i];
-          sval[j] = a.cid[(size_t)q * a.capq + i];
-          sidx[j] = i;
-        }
-      }
-    __syncthreads();
-    const int ns = (int)*s_cnt;
-    if (ns > kMergeSel) {  // uniform over the workgroup
-      if (threadIdx.x == 0) a.out_ids[(size_t)q * a.kmax] = -2;
-    } else {
-      for (int t = threadIdx.x; t < ns; t += blockDim.x) {
-        const uint64_t kt = skey[t];
-        const int64_t it = sval[t];
-        const int xt = sidx[t];
-        int rank = 0;
-        for (int j = 0; j < ns; ++j) {
-          const uint64_t kj = skey[j];
-          const int64_t ij = sval[j];
-          rank += kj < kt || (kj == kt && (ij < it || (ij == it && sidx[j] < xt)));
-        }
-        if (rank < kk) merge_emit(a, q, rank, n, kk, kt, it);
-      }
-      for (int r = kk + threadIdx.x; r < a.kmax; r += blockDim.x) merge_emit(a, q, r, n, kk, ~0ull, INT64_MAX);
-    }
-    __syncthreads();  // the LDS is reused by the next query
   }
 }
 
 // the queries k_merge left (id -2 in the first output row): a workgroup per
-// query (strided over the queries), every candidate sorted by (key, id) in
-// LDS (bitonic over the next power of two)
+// query (strided over the queries)
 __global__ __launch_bounds__(256) void k_merge_full(MergeArgs a, int nq) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  uint64_t* keys = reinterpret_cast<uint64_t*>(lds);
-  int64_t* vals = reinterpret_cast<int64_t*>(lds + a.capq * 8);
   for (int q = blockIdx.x; q < nq; q += gridDim.x) {
     const uint32_t cnt = a.ccount[q];
     const int n = (int)(cnt < a.capq ? cnt : a.capq);
     if (n <= 64 || a.out_ids[(size_t)q * a.kmax] != -2) continue;  // uniform over the workgroup
     __syncthreads();  // every thread has read the mark before it is overwritten
-    int np2 = 1;
-    while (np2 < n) np2 <<= 1;
-    for (int i = threadIdx.x; i < np2; i += blockDim.x) {
-      keys[i] = i < n ? a.ckey[(size_t)q * a.capq + i] : ~0ull;
-      vals[i] = i < n ? a.cid[(size_t)q * a.capq + i] : INT64_MAX;
-    }
-    __syncthreads();
-    block_bitonic_u64_i64(keys, vals, np2);
-    const int kk = a.kq ? a.kq[q] : a.kconst;
-    for (int r = threadIdx.x; r < a.kmax; r += blockDim.x)
-      merge_emit(a, q, r, n, kk, r < n ? keys[r] : ~0ull, r < n ? vals[r] : INT64_MAX);
-    __syncthreads();  // the LDS is reused by the next query
+    merge_sort(a, q, n, a.kq ? a.kq[q] : a.kconst, lds);
+  }
+}
+
+// all three for a small batch (at most kSmallBatch queries), a workgroup per
+// query
+__global__ __launch_bounds__(256) void k_merge_small(MergeArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  const int q = blockIdx.x, kk = a.kq ? a.kq[q] : a.kconst;
+  const uint32_t cnt = a.ccount[q];
+  if (cnt > a.capq && threadIdx.x == 0) atomicOr(&a.flags[0], 2);
+  const int n = (int)(cnt < a.capq ? cnt : a.capq);
+  if (n <= 64) {
+    if (threadIdx.x < 64) merge_wave(a, q, n, kk);
+  } else if (kk >= n || !merge_select(a, q, n, kk, lds)) {
+    merge_sort(a, q, n, kk, lds);
   }
 }
 
@@ -1995,6 +2251,62 @@ __global__ __launch_bounds__(kBaseNT, 4) void k_base_l2f(BaseL2FArgs b) {
 template <typename K>
 static void* kaddr(K k) { return reinterpret_cast<void*>(k); }
 
+// dynamic LDS limit of a kernel raised to `bytes` (only ever raised; the
+// runtime call takes microseconds of a launch-bound search, so what a kernel
+// has been given on a device is remembered)
+static hipError_t set_lds(const void* fn, size_t bytes) {
+  struct Slot {
+    const void* fn;
+    int dev;
+    size_t bytes;
+  };
+  static std::mutex mu;
+  static Slot slots[512];
+  static int n = 0;
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  std::lock_guard<std::mutex> lk(mu);
+  Slot* s = nullptr;
+  for (int i = 0; i < n && !s; ++i)
+    if (slots[i].fn == fn && slots[i].dev == dev) s = &slots[i];
+  if (s && bytes <= s->bytes) return hipSuccess;
+  e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (e != hipSuccess) return e;
+  if (!s && n < 512) {
+    s = &slots[n++];
+    s->fn = fn;
+    s->dev = dev;
+  }
+  if (s) s->bytes = bytes;
+  return hipSuccess;
+}
+
+// workgroups per CU of a kernel at a block size and dynamic LDS (remembered
+// likewise)
+static hipError_t blocks_per_cu(int* out, const void* fn, int nt, size_t lds) {
+  struct Slot {
+    const void* fn;
+    int dev, nt, blocks;
+    size_t lds;
+  };
+  static std::mutex mu;
+  static Slot slots[512];
+  static int n = 0;
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  std::lock_guard<std::mutex> lk(mu);
+  for (int i = 0; i < n; ++i)
+    if (slots[i].fn == fn && slots[i].dev == dev && slots[i].nt == nt && slots[i].lds == lds) {
+      *out = slots[i].blocks;
+      return hipSuccess;
+    }
+  if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(out, fn, nt, lds)) != hipSuccess) return e;
+  if (n < 512) slots[n++] = Slot{fn, dev, nt, *out, lds};
+  return hipSuccess;
+}
+
 hipError_t launch_prep_index(const amp_index* ix, hipStream_t st) {
   const DeviceIndex& dv = ix->dev;
   hipLaunchKernelGGL(k_sqnorm, dim3((ix->nlist + 3) / 4), dim3(256), 0, st, dv.centroids, ix->nlist,
@@ -2048,10 +2360,10 @@ static hipError_t launch_scan(int lwb, int ph, int dt, int wpr, const ScanArgs& 
   const int mt = scan_mt(mix ? 8 : lwb, sa.M, dt);
   if (!fn || variant_wpr(mt, scan_nr(mt, wpr)) != wpr) return hipErrorInvalidValue;
   size_t lds = scan_lds_bytes(lwb, ph, sa.M, sa.d, wpr, nt);
-  hipError_t e = hipFuncSetAttribute(kaddr(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipError_t e = set_lds(kaddr(fn), lds);
   if (e != hipSuccess) return e;
   int per_cu = 0;
-  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kaddr(fn), nt, lds);
+  e = blocks_per_cu(&per_cu, kaddr(fn), nt, lds);
   if (e != hipSuccess) return e;
   if (per_cu < 1) return hipErrorInvalidConfiguration;
   static const bool wg512 = [] {
@@ -2063,9 +2375,9 @@ static hipError_t launch_scan(int lwb, int ph, int dt, int wpr, const ScanArgs& 
     if (f2) {
       const size_t l2 = scan_lds_bytes(lwb, ph, sa.M, sa.d, wpr, 2 * kThreads);
       int pc2 = 0;
-      if ((e = hipFuncSetAttribute(kaddr(f2), hipFuncAttributeMaxDynamicSharedMemorySize, (int)l2)) != hipSuccess)
+      if ((e = set_lds(kaddr(f2), l2)) != hipSuccess)
         return e;
-      if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&pc2, kaddr(f2), 2 * kThreads, l2)) != hipSuccess)
+      if ((e = blocks_per_cu(&pc2, kaddr(f2), 2 * kThreads, l2)) != hipSuccess)
         return e;
       if (pc2 >= 1) {
         fn = f2;
@@ -2128,7 +2440,7 @@ static hipError_t launch_base_l2(const BaseL2Args& b, hipStream_t st) {
   const int npt = base_l2_npt(n);
   auto fn = npt == 4 ? k_base_l2<4> : (npt == 2 ? k_base_l2<2> : k_base_l2<1>);
   const size_t lds = base_l2_lds(npt);
-  const hipError_t e = hipFuncSetAttribute(kaddr(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  const hipError_t e = set_lds(kaddr(fn), lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(fn, dim3((unsigned)((n + npt * 32 - 1) / (npt * 32))), dim3(kBaseNT), lds, st, b);
   return hipGetLastError();
@@ -2139,7 +2451,7 @@ static hipError_t launch_base_l2f(const BaseL2FArgs& b, hipStream_t st) {
   const int npt = base_l2_npt(n);
   auto fn = npt == 4 ? k_base_l2f<4> : (npt == 2 ? k_base_l2f<2> : k_base_l2f<1>);
   const size_t lds = base_l2f_lds(npt);
-  const hipError_t e = hipFuncSetAttribute(kaddr(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  const hipError_t e = set_lds(kaddr(fn), lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(fn, dim3((unsigned)((n + npt * 32 - 1) / (npt * 32))), dim3(kBaseNT), lds, st, b);
   return hipGetLastError();
@@ -2156,33 +2468,44 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
   const size_t npairs = (size_t)sd.nq * sd.npmax;
   auto mark = [&](int i) { if (ev) (void)hipEventRecord(ev[i], st); };
   mark(0);
-  // resets, one launch (before anything that may raise a flag)
+  const bool ipm = sd.metric == AMP_IP;
+  const float* queries = sd.q_bf16 ? sd.q_conv : queries_in;
+  // small batches: launches fused where latency and launch gaps are the cost
+  const int64_t min_chunk = std::min(sd.chunk, sd.chunk1);
+  const bool small_q = npairs <= (size_t)kSmallQueue && NB <= kSmallBuckets &&
+                       (ix->max_list + min_chunk - 1) / min_chunk < (1 << 17);  // (32-bit unit offsets)
+  const bool small_b = sd.nq <= kSmallBatch;
   {
-    ResetArgs ra;
-    ra.cnt = reinterpret_cast<uint32_t*>(ws.cnt);
-    ra.ncnt = (size_t)2 * kQSub * NB;
-    ra.counters = ws.counters;
-    ra.ncounters = (size_t)2 * (kNCls + 1) * kQueueSlot;
-    ra.flags = reinterpret_cast<uint32_t*>(ws.flags);
-    ra.work = ws.work;
-    ra.tau = ws.tau;
-    ra.ccount = ws.ccount;
-    ra.ipmask = sd.metric == AMP_IP ? ws.ipmask : nullptr;
-    ra.nq = (size_t)sd.nq;
-    hipLaunchKernelGGL(k_reset, dim3(256), dim3(256), 0, st, ra);
-  }
-  // device-resident per-query sizes: checked, clamped and copied in
-  if (sd.k_dev) {
-    hipLaunchKernelGGL(k_sizes, dim3((sd.nq + 255) / 256), dim3(256), 0, st, sd.k_dev, sd.np_dev, ws.kq, ws.npq,
-                       sd.nq, sd.kmax, sd.npmax, ws.flags);
-  }
-  // BF16 query rows are widened first (exact)
-  const float* queries = queries_in;
-  if (sd.q_bf16) {
-    const size_t nel = (size_t)sd.nq * sd.d;
-    hipLaunchKernelGGL(k_bf16_widen, dim3((unsigned)std::min<size_t>((nel + 255) / 256, 65536)), dim3(256), 0, st,
-                       sd.q_bf16, sd.q_conv, nel);
-    queries = sd.q_conv;
+    FrontArgs f{};
+    f.cnt = reinterpret_cast<uint32_t*>(ws.cnt);
+    f.ncnt = small_q ? 0 : (size_t)2 * kQSub * NB;
+    f.counters = ws.counters;
+    f.ncounters = (size_t)2 * (kNCls + 1) * kQueueSlot;
+    f.flags = reinterpret_cast<uint32_t*>(ws.flags);
+    f.work = ws.work;
+    f.tau = ws.tau;
+    f.ccount = ws.ccount;
+    f.ipmask = ipm ? ws.ipmask : nullptr;
+    f.kin = sd.k_dev;
+    f.npin = sd.np_dev;
+    f.kout = ws.kq;
+    f.npout = ws.npq;
+    f.kmax = sd.kmax;
+    f.npmax = sd.npmax;
+    f.q = queries_in;
+    f.qb = sd.q_bf16;
+    f.qw = sd.q_conv;
+    f.qn = sd.cl_policy == AMP_CL_FP32 && sd.metric == AMP_L2 ? ws.qnorm : nullptr;  // (coarse distances)
+    f.qi = ipm && !fp32 ? ws.qi16 : nullptr;  // (predictor, table build, pair bases)
+    f.rows = f.qb || f.qn || f.qi;
+    f.nq = sd.nq;
+    f.d = sd.d;
+    f.grid_e = sd.grid_e;
+    f.grid_kind = sd.grid_kind;
+    const unsigned fb = (unsigned)std::min<size_t>(std::max<size_t>(((size_t)sd.nq + 3) / 4, 64 + f.ncnt / 4096), 16384);
+    hipLaunchKernelGGL(k_front, dim3(fb), dim3(256), 0, st, f);
+    if (f.kin && sd.nq > kFrontSizes)
+      hipLaunchKernelGGL(k_sizes, dim3((sd.nq + 255) / 256), dim3(256), 0, st, f);
   }
   // CL
   float* coarse = out_coarse ? out_coarse : ws.coarse;
@@ -2196,7 +2519,6 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
     hipLaunchKernelGGL(k_coarse_l1, dim3((sd.nlist + CL_T - 1) / CL_T, (sd.nq + CL_T - 1) / CL_T), dim3(256), 0,
                        st, queries, dv.centroids, coarse, sd.nq, sd.nlist, sd.d);
   } else {
-    hipLaunchKernelGGL(k_sqnorm, dim3((sd.nq + 3) / 4), dim3(256), 0, st, queries, sd.nq, sd.d, ws.qnorm);
     const dim3 g((sd.nlist + CL_T - 1) / CL_T, (sd.nq + CL_T - 1) / CL_T);
     const bool vec = sd.d % 4 == 0 && ((reinterpret_cast<uintptr_t>(queries) | reinterpret_cast<uintptr_t>(dv.centroids)) & 15) == 0;
     // (64-wide K chunks measured the same as 32 at 4096 x 2048 x 768)
@@ -2210,7 +2532,13 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
   mark(1);
   int np2 = 1;
   while (np2 < sd.nlist) np2 <<= 1;
-  if (sd.npmax <= 64 && sd.nlist <= 1024) {
+  // (a wave per query counts a row by itself, a workgroup splits it: one query
+  // over 1024 lists 13.7 against 7.8 us; whole searches 102 against 96 us for
+  // one query, 260 / 252 for 1024, 294 / 287 for 2048, 368 / 367 for 4096, 575 /
+  // 580 for 10000; over 256 lists they are even at 256 to 1024 queries and 241 /
+  // 249 at 4096)
+  constexpr int kTopnWg = 2048;
+  if (sd.npmax <= 64 && sd.nlist <= 1024 && (sd.nq > kTopnWg || sd.nlist <= 256)) {
     const dim3 g((sd.nq + 3) / 4), b(256);
     const int32_t* npq = ws.npq ? ws.npq : nullptr;
     if (sd.nlist <= 64)
@@ -2240,14 +2568,6 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
                        ws.npq ? ws.npq : nullptr, sd.npconst, sd.npmax, ws.probes);
   }
   mark(2);
-  const bool ipm = sd.metric == AMP_IP;
-  // inner product, integer policies: the queries on the grid (predictor,
-  // table build, pair bases)
-  if (ipm && !fp32) {
-    const size_t nel = (size_t)sd.nq * sd.d;
-    hipLaunchKernelGGL(k_qgrid, dim3((unsigned)std::min<size_t>((nel + 255) / 256, 65536)), dim3(256), 0, st, queries,
-                       ws.qi16, nel, sd.grid_e, sd.grid_kind);
-  }
   const int dt = dt_of(sd.lut_dtype);
   // lower bounds of the pairs' estimates (integer policies: the exact bases):
   // the full scan's queue is built after the phase-1 bound and leaves out the
@@ -2370,7 +2690,7 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
       // tables with their minima (and the pair bases), then the quantised tables
       const size_t tlds = base_lds_layout(kTabQ, sd.M, sd.d).total;
       auto fn = dt == DT_F16 ? k_iptab<DT_F16> : (dt == DT_F8 ? k_iptab<DT_F8> : k_iptab<DT_BF16>);
-      if ((err = hipFuncSetAttribute(kaddr(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)tlds)) != hipSuccess)
+      if ((err = set_lds(kaddr(fn), tlds)) != hipSuccess)
         return err;
       // (adaptive: the predictor pass wrote qi.ci and the width masks)
       if (sd.policy != AMP_POLICY_ADAPTIVE)
@@ -2387,7 +2707,7 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
       ba.G = G;
       const size_t blds = base_lds_layout(G, sd.M, sd.d).total;
       auto fn = k_base<DT_F8>;  // (L1 has no MFMA dtype)
-      if ((err = hipFuncSetAttribute(kaddr(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)blds)) != hipSuccess)
+      if ((err = set_lds(kaddr(fn), blds)) != hipSuccess)
         return err;
       hipLaunchKernelGGL(fn, dim3((unsigned)((npairs + G - 1) / G)), dim3(kThreads), blds, st, ba);
     }
@@ -2421,11 +2741,12 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
   qa.max_units = sd.max_units;
   qa.pbase = nullptr;
   qa.fkeys = 0;
+  qa.all_offsets = getenv("AMP_STATS") != nullptr;
   qa.tau = ws.tau;
   qa.work = nullptr;
   const int qb = (int)((npairs + 255) / 256);
   // one build of the queue phases [ph0, ph1)
-  auto build_queue = [&](int ph0, int ph1) {
+  auto build_queue = [&](int ph0, int ph1) -> hipError_t {
     QueueArgs q = qa;
     q.ph0 = ph0;
     q.ph1 = ph1;
@@ -2434,13 +2755,28 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
       q.fkeys = fp32 ? 1 : 0;
       q.work = sd.want_work ? ws.work : nullptr;
     }
+    if (small_q) {
+      // (few pairs and buckets: four waves to a barrier)
+      const int nt = npairs <= 256 && NB <= 1024 ? 256 : 1024;
+      const size_t qlds = (size_t)NB * 8 + npairs * 4;
+      auto fn = npairs <= (size_t)nt ? k_queue_small<1>
+                                     : (npairs <= 2048 ? k_queue_small<2> : k_queue_small<4>);
+      const hipError_t e = set_lds(kaddr(fn), qlds);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL(fn, dim3(1), dim3(nt), qlds, st, q, fp32 ? 1 : 0);
+      return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_qhist, dim3(qb), dim3(256), 0, st, q);
     hipLaunchKernelGGL(k_qtot, dim3(((ph1 - ph0) * NB + 255) / 256), dim3(256), 0, st, q, fp32 ? 1 : 0);
-    hipLaunchKernelGGL(k_qscan, dim3(1), dim3(1024), 0, st, q, fp32 ? 1 : 0);
+    const size_t slds = (size_t)NB * 4;
+    const hipError_t e = set_lds(kaddr(k_qscan), slds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_qscan, dim3(1), dim3(1024), slds, st, q, fp32 ? 1 : 0);
     hipLaunchKernelGGL(k_qscatter, dim3(qb), dim3(256), 0, st, q);
     hipLaunchKernelGGL(k_qunits, dim3(512), dim3(256), 0, st, q, fp32 ? 1 : 0);
+    return hipGetLastError();
   };
-  build_queue(0, early ? 1 : 2);
+  if ((err = build_queue(0, early ? 1 : 2)) != hipSuccess) return err;
   mark(5);
   // LC + DC, phase 1 then phase 2
   ScanArgs sa;
@@ -2511,15 +2847,21 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
     if ((err = launch_scan(sa_lwb, ph, dt, sd.wpr, sp, st)) != hipSuccess) return err;
     if (ph == 1) {
       // phase-1 minima -> per-query bound, buffer emptied for the candidates
-      hipLaunchKernelGGL(k_tau_wave, dim3((sd.nq + 3) / 4), dim3(256), 0, st, ws.ccount, ws.ckey, ws.tau, ws.kq,
-                         sd.kconst, sd.nq, sd.capq, ws.flags + 1);
-      // keys + digit counts + selection + list of the queries to select in
-      const size_t tlds = sd.capq * 8 + 4 * (256 + 2 + 1 + 256);
-      err = hipFuncSetAttribute(kaddr(k_tau), hipFuncAttributeMaxDynamicSharedMemorySize, (int)tlds);
-      if (err != hipSuccess) return err;
-      hipLaunchKernelGGL(k_tau, dim3(sd.nq < 1024 ? sd.nq : 1024), dim3(256), tlds, st, ws.ccount, ws.ckey, ws.tau,
-                         ws.kq, sd.kconst, sd.nq, sd.capq);
-      if (early) build_queue(1, 2);  // the full scan's queue: live pairs only
+      if (small_b) {
+        const size_t tlds = sd.capq * 8 + 4 * (256 + 2);
+        if ((err = set_lds(kaddr(k_tau_small), tlds)) != hipSuccess) return err;
+        hipLaunchKernelGGL(k_tau_small, dim3(sd.nq), dim3(256), tlds, st, ws.ccount, ws.ckey, ws.tau, ws.kq,
+                           sd.kconst, sd.capq, ws.flags + 1);
+      } else {
+        hipLaunchKernelGGL(k_tau_wave, dim3((sd.nq + 3) / 4), dim3(256), 0, st, ws.ccount, ws.ckey, ws.tau, ws.kq,
+                           sd.kconst, sd.nq, sd.capq, ws.flags + 1);
+        // keys + digit counts + selection + list of the queries to select in
+        const size_t tlds = sd.capq * 8 + 4 * (256 + 2 + 1 + 256);
+        if ((err = set_lds(kaddr(k_tau), tlds)) != hipSuccess) return err;
+        hipLaunchKernelGGL(k_tau, dim3(sd.nq < 1024 ? sd.nq : 1024), dim3(256), tlds, st, ws.ccount, ws.ckey, ws.tau,
+                           ws.kq, sd.kconst, sd.nq, sd.capq);
+      }
+      if (early && (err = build_queue(1, 2)) != hipSuccess) return err;  // the full scan's queue: live pairs only
     }
     mark(5 + ph);
     if (ph == 2) {
@@ -2529,7 +2871,7 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
       // query takes part); each re-run shrinks a query's candidate count by
       // about k / capq
       const size_t rlds = sd.capq * 16 + 4 * (256 + 2 + 1 + 256);  // keys, ids, digit counts, selection, query list
-      err = hipFuncSetAttribute(kaddr(k_retry), hipFuncAttributeMaxDynamicSharedMemorySize, (int)rlds);
+      err = set_lds(kaddr(k_retry), rlds);
       if (err != hipSuccess) return err;
       ScanArgs sr = sa;
       sr.tau_id = ws.tau_id;
@@ -2565,15 +2907,18 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
   ma2.fp32 = fp32 ? 1 : 0;
   ma2.h2 = ldexpf(1.f, sd.metric == AMP_L1 ? sd.grid_e : 2 * sd.grid_e);  // L1 estimates are in units of h
   ma2.capq = sd.capq;
-  const size_t mlds = sd.capq * 8 + kMergeSel * 20 + 4 * (256 + 3);
-  err = hipFuncSetAttribute(kaddr(k_merge), hipFuncAttributeMaxDynamicSharedMemorySize, (int)mlds);
-  if (err != hipSuccess) return err;
-  const size_t flds = sd.capq * 16;
-  err = hipFuncSetAttribute(kaddr(k_merge_full), hipFuncAttributeMaxDynamicSharedMemorySize, (int)flds);
-  if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(k_merge_wave, dim3((sd.nq + 3) / 4), dim3(256), 0, st, ma2, sd.nq);
-  hipLaunchKernelGGL(k_merge, dim3(sd.nq < 1024 ? sd.nq : 1024), dim3(256), mlds, st, ma2, sd.nq);
-  hipLaunchKernelGGL(k_merge_full, dim3(sd.nq < 512 ? sd.nq : 512), dim3(256), flds, st, ma2, sd.nq);
+  const size_t mlds = merge_select_lds(sd.capq), flds = sd.capq * 16;
+  if (small_b) {
+    const size_t slds = std::max(mlds, flds);
+    if ((err = set_lds(kaddr(k_merge_small), slds)) != hipSuccess) return err;
+    hipLaunchKernelGGL(k_merge_small, dim3(sd.nq), dim3(256), slds, st, ma2);
+  } else {
+    if ((err = set_lds(kaddr(k_merge), mlds)) != hipSuccess) return err;
+    if ((err = set_lds(kaddr(k_merge_full), flds)) != hipSuccess) return err;
+    hipLaunchKernelGGL(k_merge_wave, dim3((sd.nq + 3) / 4), dim3(256), 0, st, ma2, sd.nq);
+    hipLaunchKernelGGL(k_merge, dim3(sd.nq < 1024 ? sd.nq : 1024), dim3(256), mlds, st, ma2, sd.nq);
+    hipLaunchKernelGGL(k_merge_full, dim3(sd.nq < 512 ? sd.nq : 512), dim3(256), flds, st, ma2, sd.nq);
+  }
   if (sd.lut_export) {
     // test hook: every pair's LUT as the search builds it
     const amp_lut_export* ex = sd.lut_export;
@@ -2603,7 +2948,7 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
     } else {
       const size_t elds = base_lds_layout(kBaseExport, sd.M, sd.d).total;
       auto fn = dt == DT_F16 ? k_export<DT_F16> : (dt == DT_F8 ? k_export<DT_F8> : k_export<DT_BF16>);
-      if ((err = hipFuncSetAttribute(kaddr(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)elds)) != hipSuccess)
+      if ((err = set_lds(kaddr(fn), elds)) != hipSuccess)
         return err;
       hipLaunchKernelGGL(fn, dim3((unsigned)((npairs + kBaseExport - 1) / kBaseExport)), dim3(kThreads), elds, st, eb,
                          ex->q, ex->shift, ex->base, ex->t);
