@@ -16,7 +16,7 @@
 //    magnitudes) within the grid's largest value (255, or 448 for e4m3);
 //    integer data: h = 1;  radius max ||x - c|| in grid units, rounded.
 // Distances, assignments, the means' FP64 sums (in row order) and the radius
-// run on the GPU (build_kernels.hip), the residual codebook's k-means for all
+// run on the GPU (build_kernels.inc), the residual codebook's k-means for all
 // subspaces side by side; seeded choices and the final layout on the host.  A
 // k-means in which a cluster runs empty is repeated on the host, which reseeds
 // it.

@@ -1,4 +1,4 @@
-// Launchers of the index-build kernels (build_kernels.hip; squared norms:
+// Launchers of the index-build kernels (build_kernels.inc; squared norms:
 // kernels.hip).
 #pragma once
 #include "amp_internal.h"

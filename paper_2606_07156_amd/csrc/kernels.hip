@@ -2960,3 +2960,6 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
 }
 
 }  // namespace amp
+
+// index-build kernels and launchers
+#include "build_kernels.inc"
