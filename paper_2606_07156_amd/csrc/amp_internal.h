@@ -72,10 +72,12 @@ __host__ __device__ constexpr int lane_fields(int lwb) {
 }
 
 // -------------------------------------------------------------- device data
+constexpr int kSvWords = 8;    // words of a packed support vector
 struct DeviceModel {
   int32_t n_sv = 0;
-  int32_t* sv = nullptr;       // [n_sv][5]
-  int32_t* beta = nullptr;     // [n_sv]
+  int32_t* sv = nullptr;       // CL predictor: [n_sv][5]; LUT predictor: [n_sv][kSvWords], coordinates 0, 1 | 2, 3 in
+                               // 16-bit halves, coordinate 4, squared norm, beta
+  int32_t* beta = nullptr;     // CL predictor: [n_sv]
   int32_t* table = nullptr;    // [1024]
 };
 

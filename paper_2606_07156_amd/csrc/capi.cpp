@@ -203,12 +203,21 @@ static amp_status upload_model(amp_index* ix) {
   if (dm.table) hipFree(dm.table);
   dm = DeviceModel();
   amp_status s;
-  if ((s = dalloc(&dm.sv, 5 * (size_t)std::max(1, ix->n_sv))) != AMP_OK) return s;
-  if ((s = dalloc(&dm.beta, (size_t)std::max(1, ix->n_sv))) != AMP_OK) return s;
+  if ((s = dalloc(&dm.sv, kSvWords * (size_t)std::max(1, ix->n_sv))) != AMP_OK) return s;
   if ((s = dalloc(&dm.table, (size_t)kTableN)) != AMP_OK) return s;
   if (ix->n_sv) {
-    AMP_HIP(hipMemcpy(dm.sv, ix->sv.data(), ix->sv.size() * 4, hipMemcpyHostToDevice));
-    AMP_HIP(hipMemcpy(dm.beta, ix->beta.data(), ix->beta.size() * 4, hipMemcpyHostToDevice));
+    // one record per support vector, as the predictor kernel reads it
+    std::vector<int32_t> rec(kSvWords * (size_t)ix->n_sv, 0);
+    for (int i = 0; i < ix->n_sv; ++i) {
+      const int32_t* v = &ix->sv[5 * (size_t)i];
+      int32_t* r = &rec[kSvWords * (size_t)i];
+      r[0] = v[0] | (v[1] << 16);
+      r[1] = v[2] | (v[3] << 16);
+      r[2] = v[4];
+      r[3] = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3] + v[4] * v[4];
+      r[4] = ix->beta[i];
+    }
+    AMP_HIP(hipMemcpy(dm.sv, rec.data(), rec.size() * 4, hipMemcpyHostToDevice));
   }
   AMP_HIP(hipMemcpy(dm.table, ix->table.data(), kTableN * 4, hipMemcpyHostToDevice));
   dm.n_sv = ix->n_sv;
@@ -1099,7 +1108,6 @@ amp_status search_on(amp_index* ix, Workspace& w, const void* queries, int64_t n
   if (ix->has_model) {
     ma.n_sv = ix->n_sv;
     ma.sv = ix->dev.model.sv;
-    ma.beta = ix->dev.model.beta;
     ma.table = ix->dev.model.table;
     ma.beta0 = ix->beta0;
     for (int f = 0; f < 5; ++f) ma.feat_lo[f] = ix->feat_lo[f], ma.feat_mul[f] = ix->feat_mul[f];

@@ -654,6 +654,9 @@ __device__ __forceinline__ int64_t mitchell_q8(int64_t x) {
   return 256 * (int64_t)k + (int64_t)((y << 8) >> k) - 256;
 }
 
+typedef short s16x2 __attribute__((ext_vector_type(2)));
+typedef int i32x16 __attribute__((ext_vector_type(16)));
+
 __device__ __forceinline__ int pick_bits(int64_t y, const int64_t* theta, uint32_t allowed, int64_t margin) {
   int last = 16;
   for (int b = 4; b <= 16; b += 4) {
@@ -812,41 +815,69 @@ __global__ __launch_bounds__(256) void k_pairs(PairArgs a, ModelArgs ma) {
           int64_t v = ((mitchell_q8(x[f]) - ma.feat_lo[f]) * ma.feat_mul[f]) >> 16;
           u[f] = (int32_t)(v < 0 ? 0 : (v > 1023 ? 1023 : v));
         }
-        // integer sum: the split over threads does not change the result
-        // u and sv lie in [0, 1023] (sv checked when the model is set): the
-        // squared differences are exact 24-bit products (full-rate multiplies)
-        // and |u - sv|^2 < 2^23; g_mul < 2^32, so the table index is the high
-        // word of one 32 x 32-bit product
+        // integer sum: the split over threads and the order do not change the
+        // result.  |u - sv|^2 = |u|^2 + |sv|^2 - 2 u.sv on 16-bit pair products
+        // (u and sv lie in [0, 1023], sv checked when the model is set: exact,
+        // below 2^23), four operations instead of ten; the table index is the
+        // high word of one product with g_mul < 2^32, a full-rate 24-bit one
+        // where g_mul < 2^24 (gamma up to 63).  (Bound by the VALU with a thread
+        // per pair: 278k pairs x 1280 support vectors 169 -> 112 us; with several
+        // threads per pair by the latency of a support vector's loads, six words
+        // a vector one at a time before: 1726 pairs 52 -> 28 us.)
         const uint32_t gm = (uint32_t)ma.g_mul;
-        auto term = [&](int i) -> int64_t {
-          const int32_t* sv = ma.sv + 5 * i;
-          const int d0 = u[0] - sv[0], d1 = u[1] - sv[1], d2 = u[2] - sv[2], d3 = u[3] - sv[3], d4 = u[4] - sv[4];
-          const uint32_t dist2 = (uint32_t)(__mul24(d0, d0) + __mul24(d1, d1) + __mul24(d2, d2) + __mul24(d3, d3) +
-                                            __mul24(d4, d4));
-          const uint32_t idx = __umulhi(dist2, gm);
-          const int32_t K = s_table[idx < (uint32_t)(kTableN - 1) ? idx : (uint32_t)(kTableN - 1)];
-          return (int64_t)ma.beta[i] * K;
-        };
-        // two independent chains (an integer sum: the order does not matter)
-        int64_t y = 0, y1 = 0;
-        if (T == 1) {
-          // a thread per pair: the support-vector index is the same across the
-          // wave, so sv and beta are read through scalar loads
-          int i = 0;
-          for (; i + 1 < ma.n_sv; i += 2) {
-            y += term(i);
-            y1 += term(i + 1);
-          }
-          if (i < ma.n_sv) y += term(i);
-        } else {
+        const int un = u[0] * u[0] + u[1] * u[1] + u[2] * u[2] + u[3] * u[3] + u[4] * u[4];
+        const s16x2 u01 = {(short)(-2 * u[0]), (short)(-2 * u[1])}, u23 = {(short)(-2 * u[2]), (short)(-2 * u[3])};
+        const s16x2 u4 = {(short)(-2 * u[4]), 0};
+        auto sum = [&](auto small_g) {
+          auto term = [&](int w0, int w1, int w2, int w3, int beta) -> int64_t {
+            int d2 = un + w3;
+            d2 = __builtin_amdgcn_sdot2(u01, __builtin_bit_cast(s16x2, w0), d2, false);
+            d2 = __builtin_amdgcn_sdot2(u23, __builtin_bit_cast(s16x2, w1), d2, false);
+            d2 = __builtin_amdgcn_sdot2(u4, __builtin_bit_cast(s16x2, w2), d2, false);
+            const uint32_t idx = decltype(small_g)::value ? __umulhi((uint32_t)d2 & 0xFFFFFFu, gm & 0xFFFFFFu)
+                                                          : __umulhi((uint32_t)d2, gm);
+            return (int64_t)beta * s_table[idx < (uint32_t)(kTableN - 1) ? idx : (uint32_t)(kTableN - 1)];
+          };
+          int64_t y = 0;
           int i = t;
-          for (; i + T < ma.n_sv; i += 2 * T) {
-            y += term(i);
-            y1 += term(i + T);
+          if (T == 1) {
+            // a thread per pair: the support-vector index is the same across
+            // the wave, so records come through scalar loads, two per load
+            // (one word at a time, each load was waited for alone)
+            const i32x16* rec = reinterpret_cast<const i32x16*>(ma.sv);
+            for (; i + 3 < ma.n_sv; i += 4) {
+              const i32x16 r0 = rec[i / 2], r1 = rec[i / 2 + 1];
+              y += term(r0[0], r0[1], r0[2], r0[3], r0[4]);
+              y += term(r0[8], r0[9], r0[10], r0[11], r0[12]);
+              y += term(r1[0], r1[1], r1[2], r1[3], r1[4]);
+              y += term(r1[8], r1[9], r1[10], r1[11], r1[12]);
+            }
+          } else {
+            const int4* rec = reinterpret_cast<const int4*>(ma.sv);
+            // eight records on the way per thread; past the end the last one
+            // again, with weight zero
+            constexpr int UN = 8;
+            for (; i < ma.n_sv; i += UN * T) {
+              int4 r[UN];
+              int bt[UN];
+#pragma unroll
+              for (int k = 0; k < UN; ++k) {
+                const int e = i + k * T < ma.n_sv ? i + k * T : ma.n_sv - 1;
+                r[k] = rec[2 * e];
+                bt[k] = ma.sv[kSvWords * e + 4];
+              }
+#pragma unroll
+              for (int k = 0; k < UN; ++k)
+                y += term(r[k].x, r[k].y, r[k].z, r[k].w, i + k * T < ma.n_sv ? bt[k] : 0);
+            }
           }
-          if (i < ma.n_sv) y += term(i);
-        }
-        y += y1;
+          for (; i < ma.n_sv; i += T) {
+            const int32_t* w = ma.sv + kSvWords * i;
+            y += term(w[0], w[1], w[2], w[3], w[4]);
+          }
+          return y;
+        };
+        int64_t y = gm < (1u << 24) ? sum(std::true_type{}) : sum(std::false_type{});
         for (int o = 1; o < T; o <<= 1) y += __shfl_xor(y, o);
         bits = (uint8_t)pick_bits(ma.beta0 + y, ma.theta, a.allowed, a.margin);
       }
@@ -1949,7 +1980,7 @@ inline size_t base_l2_lds(int npt) { return (size_t)npt * 32 * (base_l2_row() + 
 template <int NPT>
 __global__ __launch_bounds__(kBaseNT, 4) void k_base_l2(BaseL2Args b) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  constexpr int G = NPT * 32, ROW = base_l2_row(), NW = kBaseNT / 64;
+  constexpr int G = NPT * 32, ROW = base_l2_row(), NW = kBaseNT / 64, RU = NPT < 4 ? NPT : 4;
   unsigned long long* smin = reinterpret_cast<unsigned long long*>(lds + G * ROW);  // [G] sum of the minima
   int64_t* srr = reinterpret_cast<int64_t*>(smin + G);                              // [G] sum of |ri|^2
   int32_t* sp = reinterpret_cast<int32_t*>(srr + G);                                // [G] list of the pair, or -1
@@ -1981,7 +2012,7 @@ __global__ __launch_bounds__(kBaseNT, 4) void k_base_l2(BaseL2Args b) {
     const int cd4 = (cm * ds) >> 2, o4 = (m0 * ds) >> 2;  // M and the chunk are multiples of 4
     __syncthreads();  // the last chunk's rows are read (first chunk: the lists are in)
     // residuals onto the grid: sixteen lanes per pair, two 16-byte reads each
-#pragma unroll(NPT < 4 ? NPT : 4)
+#pragma unroll RU
     for (int u = 0; u < G / (kBaseNT / 16) + (G < kBaseNT / 16); ++u) {
       const int g = grp + u * (kBaseNT / 16);
       if (g >= G) break;
@@ -2097,7 +2128,7 @@ inline size_t base_l2f_lds(int npt) {
 template <int NPT>
 __global__ __launch_bounds__(kBaseNT, 4) void k_base_l2f(BaseL2FArgs b) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  constexpr int G = NPT * 32, ROW = base_l2f_row(), NW = kBaseNT / 64;
+  constexpr int G = NPT * 32, ROW = base_l2f_row(), NW = kBaseNT / 64, RU = NPT < 2 ? NPT : 2;
   float* rr = reinterpret_cast<float*>(lds + G * ROW);  // [G][kBaseRr]
   float* part = rr + G * kBaseRr;                       // [NW][G] sums of the waves
   float* srr = part + NW * G;                           // [G] sum of |r|^2
@@ -2121,7 +2152,7 @@ __global__ __launch_bounds__(kBaseNT, 4) void k_base_l2f(BaseL2FArgs b) {
     const int cm = b.M - m0 < kBaseCM ? b.M - m0 : kBaseCM;
     const int cd4 = (cm * ds) >> 2, o4 = (m0 * ds) >> 2;
     __syncthreads();
-#pragma unroll(NPT < 2 ? NPT : 2)
+#pragma unroll RU
     for (int u = 0; u < NPT; ++u) {
       const int g = grp + u * (kBaseNT / 16);
       const int p = sp[g] < 0 ? 0 : sp[g];
