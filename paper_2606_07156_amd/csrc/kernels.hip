@@ -36,7 +36,9 @@ struct FrontArgs {
   uint64_t* work;    // [4] -> 0
   uint64_t* tau;     // [nq] -> no bound
   uint32_t* ccount;  // [nq] -> 0
-  int32_t* ipmask;   // [nq] -> 0, or null
+  int32_t* ipmask;   // [nq] -> 0, or null (with the table reductions below)
+  int32_t* ipspan;   // [nq] -> 0
+  int64_t* iplsum;   // [nq] -> 0
   const int32_t* kin;   // device sizes, or null: each k into [1, kmax] and
   const int32_t* npin;  // nprobe into [1, npmax] (flag 32 if one was outside)
   int32_t* kout;
@@ -78,7 +80,11 @@ __global__ __launch_bounds__(256) void k_front(FrontArgs a) {
   for (size_t i = i0; i < (size_t)a.nq; i += st) {
     a.tau[i] = ~0ull;
     a.ccount[i] = 0;
-    if (a.ipmask) a.ipmask[i] = 0;
+    if (a.ipmask) {
+      a.ipmask[i] = 0;
+      a.ipspan[i] = 0;
+      a.iplsum[i] = 0;
+    }
   }
   if (!a.rows) return;
   const int lane = threadIdx.x & 63;
@@ -884,7 +890,7 @@ __global__ __launch_bounds__(256) void k_pairs(PairArgs a, ModelArgs ma) {
     }
     if (t == 0) a.pbits[(size_t)q * a.npmax + r] = bits;
     if (a.dot_out && p >= 0 && t == 0) {
-      // the pair's list term for its base (k_iptab subtracts it from the sum
+      // the pair's list term for its base (k_ipq subtracts it from the sum
       // of the query's row minima) and its width in the query slot's mask
       a.dot_out[(size_t)q * a.npmax + r] = dot;
       atomicOr(&s_wmask[slot], 1 << ((bits >> 2) - 1));
@@ -1774,24 +1780,136 @@ __global__ void k_qgrid(const float* __restrict__ Q, int16_t* __restrict__ qi, s
     qi[i] = (int16_t)grid_val(Q[i], grid_e, grid_kind);
 }
 
-// inner product, FP32 policy: each query's dot products q_m . c_mj in FP32
-// (the FMA chain of the scan's FP32 entries, in the same order)
-__global__ void k_iptab_f32(BaseArgs b) {
-  const size_t n = (size_t)b.nq * b.M * kKsub;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const size_t q = i / ((size_t)b.M * kKsub);
-    const int e = (int)(i - q * b.M * kKsub), m = e >> 8;
-    const float* r = b.Q + q * b.d + m * b.dsub;
-    const float* c = b.codebook + (size_t)e * b.dsub;
-    float dot = 0.f;
+constexpr int kTabQ = 8;  // queries per workgroup of the table build (one 8-row MFMA tile)
+
+// inner product, integer policies: each query's exact table T[m][j] =
+// -qi_m . cbi_mj (LUT pass 1 on MFMA, the entries kept) and its row minima;
+// the largest row span and the sum of the minima are gathered per query with
+// one atomic each (k_ipq completes the pair bases from them).  mps m-pairs of
+// the table per workgroup: all of them where the queries alone fill the chip
+// (the codebook fragments, M * 8 KB, are read once per eight queries), fewer
+// for small batches, whose workgroups were each a chain of M / 8 steps on an
+// otherwise idle chip (M 96: 300 queries 69 us with 38 workgroups, 14 with 456;
+// 4096 queries 98 us with one workgroup per eight queries, 88 with the
+// pair bases formed by k_ipq)
+template <int DT>
+__global__ __launch_bounds__(kThreads) void k_iptab(BaseArgs b, int mps) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  const ScanLds L = base_lds_layout(kTabQ, b.M, b.d);
+  ScanArgs a{};
+  a.d = b.d;
+  a.dsub = b.dsub;
+  a.M = b.M;
+  a.tab_out = b.iptab;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int M = b.M;
+  const int q0 = blockIdx.x * kTabQ;
+  const int nqb = b.nq - q0 < kTabQ ? b.nq - q0 : kTabQ;
+  const int mp0 = blockIdx.y * mps, mp1 = mp0 + mps < M / 2 ? mp0 + mps : M / 2;
+  int32_t* pq = reinterpret_cast<int32_t*>(lds + L.pq);
+  if (tid < kTabQ) pq[tid] = q0 + tid;
+  const int d4 = b.d >> 2, rs4 = ri_stride(b.d) >> 2;
+  for (int e = tid; e < kTabQ * d4; e += kThreads) {
+    const int g = e / d4, t4 = e - g * d4;
+    u32x2 v = {0u, 0u};
+    if (g < nqb) v = reinterpret_cast<const u32x2*>(b.qi16 + (size_t)(q0 + g) * b.d)[t4];
+    reinterpret_cast<u32x2*>(lds + L.ri)[g * rs4 + t4] = v;
+  }
+  __syncthreads();
+  for (int mp = mp0 + wave; mp < mp1; mp += kThreads / 64) {
+    u32x4 Bt[16], Bd[16];
+    base_frags<DT>(b, mp, lane, Bt, Bd);
+    lut_mpair<32, kTabQ, DT, 4, true>(a, lds, L, M, nqb, mp, Bt, Bd);
+  }
+  __syncthreads();
+  const int32_t* lo = reinterpret_cast<const int32_t*>(lds + L.lo);
+  const int32_t* hi = reinterpret_cast<const int32_t*>(lds + L.hi);
+  // per query (a wave each): span and sum of minima (per-subspace
+  // granularity: the sum of the row spans instead of the largest)
+  for (int g = wave; g < nqb; g += kThreads / 64) {
+    int32_t span = 0;
+    int64_t sum = 0, rsum = 0;
+    for (int m = 2 * mp0 + lane; m < 2 * mp1; m += 64) {
+      const int32_t l = lo[g * M + m], h = hi[g * M + m];
+      b.iplo[(size_t)(q0 + g) * M + m] = l;
+      span = h - l > span ? h - l : span;
+      rsum += h - l;
+      sum += l;
+    }
 #pragma unroll
-    for (int t = 0; t < kMaxDsub; ++t)
-      if (t < b.dsub) dot = fmaf(r[t], c[t], dot);
-    b.iptab[i] = __float_as_int(dot);
+    for (int off = 32; off > 0; off >>= 1) {
+      const int32_t o = __shfl_xor(span, off);
+      span = o > span ? o : span;
+      sum += __shfl_xor(sum, off);
+      rsum += __shfl_xor(rsum, off);
+    }
+    if (lane == 0) {
+      if (b.gran) atomicAdd(&b.ipspan[q0 + g], (int32_t)rsum);
+      else atomicMax(&b.ipspan[q0 + g], span);
+      atomicAdd(reinterpret_cast<unsigned long long*>(&b.iplsum[q0 + g]), (unsigned long long)sum);
+    }
   }
 }
 
-// inner product: qi.ci of each pair (exact integers; k_iptab subtracts it
+// inner product, FP32 policy: each query's dot products q_m . c_mj in FP32
+// (the FMA chain of the scan's FP32 entries, in the same order) and the
+// largest of each row
+// A thread holds one codeword of subspace m in registers and walks over the
+// workgroup's queries, whose coordinates are uniform (scalar loads): bound by
+// the table writes (1024 queries x 96 x 256: 100 MB, 21 us at the copy rate;
+// a thread per entry with both operands read from memory, and the rows read again
+// for their maxima, took 359 us; 36 now).
+constexpr int kTabF = 32;  // queries per workgroup (a multiple of four)
+
+// largest of the wave's 64 values on lane 63 (a lane without a source in a step
+// keeps its own; NaN is passed over)
+__device__ __forceinline__ float wave_max63(float x) {
+  auto step = [&](auto ctrl) {
+    const int xi = __float_as_int(x);
+    x = fmaxf(x, __int_as_float(__builtin_amdgcn_update_dpp(xi, xi, decltype(ctrl)::value, 0xF, 0xF, false)));
+  };
+  step(std::integral_constant<int, 0x111>{});  // within rows of sixteen: 1, 2, 4, 8 to the right
+  step(std::integral_constant<int, 0x112>{});
+  step(std::integral_constant<int, 0x114>{});
+  step(std::integral_constant<int, 0x118>{});
+  step(std::integral_constant<int, 0x142>{});  // a row's last lane to the next row
+  step(std::integral_constant<int, 0x143>{});  // lane 31 to the upper half
+  return x;
+}
+
+template <int DS>  // dsub
+__global__ __launch_bounds__(256) void k_iptab_f32(BaseArgs b) {
+  __shared__ float s_mx[kTabF][4];
+  const int m = blockIdx.x, j = threadIdx.x, lane = j & 63;
+  const int q0 = blockIdx.y * kTabF, nqb = b.nq - q0 < kTabF ? b.nq - q0 : kTabF;
+  float c[DS];
+#pragma unroll
+  for (int t = 0; t < DS; ++t) c[t] = b.codebook[((size_t)m * kKsub + j) * DS + t];
+  float* out = reinterpret_cast<float*>(b.iptab);
+  for (int g0 = 0; g0 < nqb; g0 += 4) {
+    float dot[4] = {0.f, 0.f, 0.f, 0.f};
+    // (past the last query: its row again, not stored)
+    const float* r[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) r[u] = b.Q + (size_t)(q0 + (g0 + u < nqb ? g0 + u : nqb - 1)) * b.d + m * DS;
+#pragma unroll
+    for (int t = 0; t < DS; ++t)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) dot[u] = fmaf(r[u][t], c[t], dot[u]);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (g0 + u < nqb) out[((size_t)(q0 + g0 + u) * b.M + m) * kKsub + j] = dot[u];
+      const float mx = wave_max63(dot[u]);
+      if (lane == 63) s_mx[g0 + u][j >> 6] = mx;
+    }
+  }
+  __syncthreads();
+  if (j < nqb)
+    reinterpret_cast<float*>(b.iplo)[(size_t)(q0 + j) * b.M + m] =
+        fmaxf(fmaxf(s_mx[j][0], s_mx[j][1]), fmaxf(s_mx[j][2], s_mx[j][3]));
+}
+
+// inner product: qi.ci of each pair (exact integers; k_ipq subtracts it
 // from the sum of the query's row minima: the pair's base), for the
 // policies whose predictor pass does not compute it.  A workgroup per query,
 // sixteen lanes per probed list (sixteen lists per step); the widths the
@@ -1824,7 +1942,7 @@ __global__ __launch_bounds__(256) void k_ipbase(BaseArgs b) {
 #pragma unroll
     for (int off = 8; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 16);
     if (p >= 0 && r == 0) {
-      b.pbase[i] = acc;  // qi.ci: k_iptab turns it into the base once the query's minima are known
+      b.pbase[i] = acc;  // qi.ci: k_ipq turns it into the base once the query's minima are known
       mask |= 1 << ((b.pbits[i] >> 2) - 1);
     }
   }
@@ -1833,20 +1951,56 @@ __global__ __launch_bounds__(256) void k_ipbase(BaseArgs b) {
   if (tid == 0 && s_mask) atomicOr(&b.ipmask[q], s_mask);
 }
 
-// inner product, FP32 policy: the largest dot product of each (query,
-// subspace) row of the query's FP32 table (a wave per row)
-__global__ __launch_bounds__(256) void k_ipmax_f32(BaseArgs b) {
-  const int lane = threadIdx.x & 63;
-  const size_t row = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= (size_t)b.nq * b.M) return;
-  const float* t = reinterpret_cast<const float*>(b.iptab) + row * kKsub;
-  float mx = fmaxf(fmaxf(t[lane], t[lane + 64]), fmaxf(t[lane + 128], t[lane + 192]));
+// inner product, FP32 policy: the key of a lower bound of each pair's in-order
+// FP32 sums, from the pair's coarse distance D = -q.c: D - sum_m max_j dot_mj
+// less a slack for every rounding on the way (a workgroup per query).  Rounding
+// is monotone, so the scan's in-order sum of a vector's entries is at least that
+// of the rows' smallest ones.  With mag = |q| |c| + sum_m |max_j dot_mj| the
+// coarse sum differs from the exact one by at most d roundings of 2^-24 mag, the
+// scan's list term by dsub + M, its sum of M entries by M, the sum here by
+// M / 256 + 8; twice their count is taken, and norms below which squares
+// underflow count as 1e-17.  Not finite, or near overflow: key 0, the scan
+// decides.  (The bound by the scan's own arithmetic read every pair's rows again
+// and added 2 M terms one after the other on every lane: 768 us for 143k pairs,
+// d 768, M 96; 5 now, with the same 107k pairs left out.)
+__global__ __launch_bounds__(256) void k_ipbound_f32(BaseArgs b, const float* __restrict__ coarse,
+                                                     const float* __restrict__ qn, const float* __restrict__ cn,
+                                                     int nlist) {
+  __shared__ float s_s[4], s_a[4];
+  const size_t q = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const float* mx = reinterpret_cast<const float*>(b.iplo) + q * b.M;
+  float s = 0.f, ab = 0.f;
+  for (int m = tid; m < b.M; m += 256) {
+    s += mx[m];
+    ab += fabsf(mx[m]);
+  }
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-  if (lane == 0) reinterpret_cast<float*>(b.iplo)[row] = mx;
+  for (int off = 32; off > 0; off >>= 1) {
+    s += __shfl_xor(s, off);
+    ab += __shfl_xor(ab, off);
+  }
+  if (lane == 0) {
+    s_s[tid >> 6] = s;
+    s_a[tid >> 6] = ab;
+  }
+  __syncthreads();
+  s = (s_s[0] + s_s[1]) + (s_s[2] + s_s[3]);
+  ab = (s_a[0] + s_a[1]) + (s_a[2] + s_a[3]);
+  const float u = (float)(b.d + b.dsub + 2 * b.M + 64) * 0x1p-23f;
+  const float qq = qn[q];
+  for (int j = tid; j < b.npmax; j += 256) {
+    const size_t i = q * b.npmax + j;
+    const int p = b.probes[i];
+    if (p < 0) continue;
+    const float mag = (sqrtf(qq) + 1e-17f) * (sqrtf(cn[p]) + 1e-17f) * 1.001f + ab;
+    const float lb = (coarse[q * nlist + p] - s) - (mag * u + 1e-30f * (float)b.M);
+    const bool ok = mag < 1e30f && qq < 1e37f && cn[p] < 1e37f && lb > -1e37f && lb < 1e37f;  // false for NaN
+    b.pbase[i] = ok ? (int64_t)fkey(lb) : 0;
+  }
 }
 
-// inner product, FP32 policy: the key of each pair's lower bound, computed
+// the same where the coarse distances are integer ones, computed
 // with the scan's own FP32 arithmetic (a wave per pair): the pair's base
 // term bf = sum over the subspaces (in order) of the FMA chain of -q_t c_t,
 // then the in-order sum over the subspaces of the smallest LUT entry,
@@ -1904,6 +2058,10 @@ __global__ void k_export_ip(BaseArgs b, uint16_t* exq, int32_t* exs, int64_t* ex
 // eight entries per thread, read once and written at every width the query
 // needs
 __global__ void k_ipq(BaseArgs b) {
+  // the pair bases: sum of the query's row minima - qi.ci (pbase held qi.ci)
+  const size_t np = (size_t)b.nq * b.npmax;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < np; i += (size_t)gridDim.x * blockDim.x)
+    if (b.probes[i] >= 0) b.pbase[i] = b.iplsum[i / b.npmax] - b.pbase[i];
   const size_t per = (size_t)b.M * kKsub / 8;
   const size_t n = (size_t)b.nq * per;
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
@@ -2517,6 +2675,8 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
     f.tau = ws.tau;
     f.ccount = ws.ccount;
     f.ipmask = ipm ? ws.ipmask : nullptr;
+    f.ipspan = ws.ipspan;
+    f.iplsum = ws.iplsum;
     f.kin = sd.k_dev;
     f.npin = sd.np_dev;
     f.kout = ws.kq;
@@ -2526,7 +2686,8 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
     f.q = queries_in;
     f.qb = sd.q_bf16;
     f.qw = sd.q_conv;
-    f.qn = sd.cl_policy == AMP_CL_FP32 && sd.metric == AMP_L2 ? ws.qnorm : nullptr;  // (coarse distances)
+    // (coarse distances of L2; pair bounds of the FP32 policy under inner product)
+    f.qn = sd.cl_policy == AMP_CL_FP32 && (sd.metric == AMP_L2 || (ipm && fp32)) ? ws.qnorm : nullptr;
     f.qi = ipm && !fp32 ? ws.qi16 : nullptr;  // (predictor, table build, pair bases)
     f.rows = f.qb || f.qn || f.qi;
     f.nq = sd.nq;
@@ -2711,11 +2872,17 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
     } else if (ipm && fp32) {
       // the queries' FP32 dot-product tables, their row maxima, the pairs'
       // FP32 lower bounds
-      const size_t n = (size_t)sd.nq * sd.M * kKsub;
-      hipLaunchKernelGGL(k_iptab_f32, dim3((unsigned)std::min<size_t>((n + 255) / 256, 1 << 20)), dim3(256), 0, st,
-                         ba);
-      hipLaunchKernelGGL(k_ipmax_f32, dim3((unsigned)(((size_t)sd.nq * sd.M + 3) / 4)), dim3(256), 0, st, ba);
-      hipLaunchKernelGGL(k_ipbase_f32, dim3((unsigned)((npairs + 3) / 4)), dim3(256), 0, st, ba);
+      static_assert(kMaxDsub == 8, "a table kernel per subspace width");
+      constexpr decltype(&k_iptab_f32<1>) kTab[kMaxDsub] = {k_iptab_f32<1>, k_iptab_f32<2>, k_iptab_f32<3>,
+                                                            k_iptab_f32<4>, k_iptab_f32<5>, k_iptab_f32<6>,
+                                                            k_iptab_f32<7>, k_iptab_f32<8>};
+      const auto tab = kTab[sd.dsub - 1];
+      hipLaunchKernelGGL(tab, dim3((unsigned)sd.M, (unsigned)((sd.nq + kTabF - 1) / kTabF)), dim3(256), 0, st, ba);
+      if (sd.cl_policy == AMP_CL_FP32)
+        hipLaunchKernelGGL(k_ipbound_f32, dim3((unsigned)sd.nq), dim3(256), 0, st, ba, coarse, ws.qnorm, dv.cnorm,
+                           sd.nlist);
+      else
+        hipLaunchKernelGGL(k_ipbase_f32, dim3((unsigned)((npairs + 3) / 4)), dim3(256), 0, st, ba);
     } else if (ipm) {
       // the pairs' qi.ci and the widths each query needs, then the queries'
       // tables with their minima (and the pair bases), then the quantised tables
@@ -2726,7 +2893,10 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
       // (adaptive: the predictor pass wrote qi.ci and the width masks)
       if (sd.policy != AMP_POLICY_ADAPTIVE)
         hipLaunchKernelGGL(k_ipbase, dim3((unsigned)sd.nq), dim3(256), 0, st, ba);
-      hipLaunchKernelGGL(fn, dim3((sd.nq + kTabQ - 1) / kTabQ), dim3(kThreads), tlds, st, ba);
+      // (at least four m-pairs, one per wave, and no more workgroups than twice the chip)
+      const int groups = (sd.nq + kTabQ - 1) / kTabQ, ys = std::max(1, std::min(512 / groups, sd.M / 8));
+      const int mps = (((sd.M / 2 + ys - 1) / ys) + 3) & ~3;
+      hipLaunchKernelGGL(fn, dim3(groups, (sd.M / 2 + mps - 1) / mps), dim3(kThreads), tlds, st, ba, mps);
       const size_t nq8 = (size_t)sd.nq * sd.M * kKsub / 8;
       hipLaunchKernelGGL(k_ipq, dim3((unsigned)std::min<size_t>((nq8 + 255) / 256, 1 << 20)), dim3(256), 0, st, ba);
     } else if (early && !fp32) {

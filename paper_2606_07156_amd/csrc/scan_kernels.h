@@ -1854,75 +1854,4 @@ __global__ __launch_bounds__(kThreads) void k_export(BaseArgs b, uint16_t* exq, 
   }
 }
 
-constexpr int kTabQ = 8;  // queries per workgroup of the table build (one 8-row MFMA tile)
-
-// inner product, integer policies: each query's exact table T[m][j] =
-// -qi_m . cbi_mj (LUT pass 1 on MFMA, the entries kept), its row minima, the
-// largest row span and the sum of the minima; the pair bases, which held
-// qi.ci, become the sum of the minima - qi.ci
-template <int DT>
-__global__ __launch_bounds__(kThreads) void k_iptab(BaseArgs b) {
-  extern __shared__ __attribute__((aligned(16))) char lds[];
-  const ScanLds L = base_lds_layout(kTabQ, b.M, b.d);
-  ScanArgs a{};
-  a.d = b.d;
-  a.dsub = b.dsub;
-  a.M = b.M;
-  a.tab_out = b.iptab;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int M = b.M;
-  const int q0 = blockIdx.x * kTabQ;
-  const int nqb = b.nq - q0 < kTabQ ? b.nq - q0 : kTabQ;
-  int32_t* pq = reinterpret_cast<int32_t*>(lds + L.pq);
-  if (tid < kTabQ) pq[tid] = q0 + tid;
-  const int d4 = b.d >> 2, rs4 = ri_stride(b.d) >> 2;
-  for (int e = tid; e < kTabQ * d4; e += kThreads) {
-    const int g = e / d4, t4 = e - g * d4;
-    u32x2 v = {0u, 0u};
-    if (g < nqb) v = reinterpret_cast<const u32x2*>(b.qi16 + (size_t)(q0 + g) * b.d)[t4];
-    reinterpret_cast<u32x2*>(lds + L.ri)[g * rs4 + t4] = v;
-  }
-  __syncthreads();
-  for (int mp = wave; mp < M / 2; mp += kThreads / 64) {
-    u32x4 Bt[16], Bd[16];
-    base_frags<DT>(b, mp, lane, Bt, Bd);
-    lut_mpair<32, kTabQ, DT, 4, true>(a, lds, L, M, nqb, mp, Bt, Bd);
-  }
-  __syncthreads();
-  const int32_t* lo = reinterpret_cast<const int32_t*>(lds + L.lo);
-  const int32_t* hi = reinterpret_cast<const int32_t*>(lds + L.hi);
-  for (int e = tid; e < nqb * M; e += kThreads) b.iplo[(size_t)q0 * M + e] = lo[e];
-  // per query (a wave each): span and sum of minima
-  // (per-subspace granularity: the sum of the row spans instead of the
-  // largest)
-  for (int g = wave; g < nqb; g += kThreads / 64) {
-    int32_t span = 0;
-    int64_t sum = 0, rsum = 0;
-    for (int m = lane; m < M; m += 64) {
-      span = hi[g * M + m] - lo[g * M + m] > span ? hi[g * M + m] - lo[g * M + m] : span;
-      rsum += hi[g * M + m] - lo[g * M + m];
-      sum += lo[g * M + m];
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      const int32_t o = __shfl_xor(span, off);
-      span = o > span ? o : span;
-      sum += __shfl_xor(sum, off);
-      rsum += __shfl_xor(rsum, off);
-    }
-    if (lane == 0) {
-      b.ipspan[q0 + g] = b.gran ? rsum : span;
-      b.iplsum[q0 + g] = sum;
-      reinterpret_cast<int64_t*>(lds + L.rr)[g] = sum;  // (rr is not used by the inner-product build)
-    }
-  }
-  __syncthreads();
-  // the pair bases: sum of the query's row minima - qi.ci (pbase held qi.ci)
-  const int64_t* psum = reinterpret_cast<const int64_t*>(lds + L.rr);
-  for (int e = tid; e < nqb * b.npmax; e += kThreads) {
-    const size_t i = (size_t)q0 * b.npmax + e;
-    if (b.probes[i] >= 0) b.pbase[i] = psum[e / b.npmax] - b.pbase[i];
-  }
-}
-
 }  // namespace amp

@@ -1,0 +1,57 @@
+"""Inner product's tables per query.  Integer policies: the table build split
+over subspaces gives the answers of the oracle (a few queries) and of the unsplit
+build (a batch that fills the chip), at numbers of subspaces that a split does
+not divide.  FP32 policy: the pairs left out by the bound from the coarse
+distance change nothing, at every subspace width, at edges of the table
+kernel's groups of four and 32 queries, for data far from the origin (where the
+bound's slack is large against the distances' differences) and odd queries."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2606_07156_amd as amp
+from test_gpu_pair_bounds import random_index
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,dsub", [(4, 8), (8, 8), (20, 3), (36, 4), (96, 8), (120, 8)])
+@pytest.mark.parametrize("gran", ["pair", "subspace"])
+def test_split_table_build(M, dsub, gran):
+    idx = random_index(M, M, dsub, metric="ip", n=3000)
+    h = amp.amp_index_from_arrays(idx)
+    r = np.random.default_rng(M)
+    Q = (idx["centroids"][r.integers(1, 40, 4100)] + r.standard_normal((4100, idx["d"]))).astype(np.float32)
+    kw = dict(policy="fixed", bits=8, granularity=gran, want_probes=True)
+    full = amp.amp_search(h, Q, 10, 6, **kw)  # 513 groups of eight: one workgroup each
+    for nq in (1, 9):
+        part = amp.amp_search(h, Q[:nq], 10, 6, **kw)
+        for f in ("ids", "dist", "qdist", "probes"):
+            assert np.array_equal(part[f], full[f][:nq]), (nq, f)
+    if gran == "pair":
+        ref = oracle.search(idx, Q[:3], 10, 6, policy="fixed", bits=8, probes=full["probes"][:3])
+        assert np.array_equal(full["ids"][:3], ref["ids"])
+
+
+@pytest.mark.parametrize("M,dsub", [(16, 8), (24, 7), (8, 6), (32, 5), (24, 4), (20, 3), (36, 2), (12, 1), (96, 8)])
+@pytest.mark.parametrize("offset", [0.0, 30.0])
+def test_fp32_bound_from_the_coarse_distance(monkeypatch, M, dsub, offset):
+    idx = random_index(M + dsub, M, dsub, metric="ip")
+    idx["centroids"] = (idx["centroids"] + offset).astype(np.float32)
+    h = amp.amp_index_from_arrays(idx)
+    r = np.random.default_rng(M)
+    dead = 0
+    for nq in (1, 5, 31, 33, 700):
+        Q = (idx["centroids"][r.integers(0, 40, nq)] + r.standard_normal((nq, idx["d"]))).astype(np.float32)
+        if nq == 33:
+            Q[2, 1], Q[3] = -1e30, 1e-25  # no usable bound, squares that underflow
+        np_q = np.full(nq, 12, np.int32)
+        np_q[1::3] = 5
+        got = amp.amp_search(h, Q, 5, np_q, policy="fp32", work=True)
+        monkeypatch.setenv("AMP_PAIR_SKIP", "0")
+        want = amp.amp_search(h, Q, 5, np_q, policy="fp32")
+        monkeypatch.delenv("AMP_PAIR_SKIP")
+        for f in ("ids", "dist"):
+            assert np.array_equal(got[f], want[f], equal_nan=f == "dist"), (nq, f)
+        dead += got["work"]["dead_pairs"]
+    assert dead > 0
