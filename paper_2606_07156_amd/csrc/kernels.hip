@@ -3018,6 +3018,7 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
   sa.work = nullptr;
   sa.steal = sd.queue;
   sa.iptab = ws.iptab;
+  sa.iplo = ws.iplo;
   sa.iptq = ws.iptq;
   sa.ipsh = ws.ipsh;
   sa.pbase_g = ws.pbase;

@@ -36,6 +36,7 @@ struct ScanArgs {
   // with its row minima and span; FP32 policy: FP32 dot products), and the
   // pairs' exact bases
   const int32_t* iptab;     // [nq][M][256] (FP32 policy: the FP32 dot products)
+  const int32_t* iplo;      // [nq][M] (FP32 policy: each row's largest dot product)
   const uint16_t* iptq;     // [nq][4][M][256] quantised tables per width (bytes where ip_bytes)
   const int32_t* ipsh;      // [nq][4] their shifts
   const int64_t* pbase_g;   // [nq][npmax]
@@ -595,7 +596,10 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
     // and centroids 16-byte aligned); (pair, quad) advanced without division
     const bool ip = a.metric == AMP_IP;
     const bool l1 = a.metric == AMP_L1;
-    if (FP || !ip) {
+    // FP32 inner product, one pair per unit: the LUT is copied from the
+    // query's table (below), without residual rows
+    const bool tabcopy = FP && WPR == 1 && ip;
+    if ((FP || !ip) && !tabcopy) {
       const int d4 = a.d >> 2;
       const int gstep = NT / d4, tstep = NT - gstep * d4;
       int g = tid / d4, t4 = tid - g * d4;
@@ -663,7 +667,81 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
       if (PHASE >= 2 && tid < G) pair_threshold(tid);
     };
     // ---- LC
-    if constexpr (FP) {
+    if constexpr (FP && WPR == 1) {
+      // inner product, one pair per unit: entries 0 - dot, of subspace 0
+      // bf - dot with the pair's list term bf = -q.c (subspace partials added in
+      // order).  All waves but the first copy the rows of the query's table,
+      // 16 bytes a lane and eight loads ahead; the first wave meanwhile sums bf
+      // and the pair's lower bound (rows' smallest entries, from the largest dot
+      // products, in the scan's subspace order), then writes row 0.  (Entry by
+      // entry behind the residual stage, with the minima read back from the LUT,
+      // a unit of 2200 vectors took 29 us, most of it waiting for one load after
+      // another: 4021 us for 36k units, d 768, M 96; 2064 now, near what the
+      // LDS reads of the scan itself take.)
+      if (tabcopy) {
+        const float4* src = reinterpret_cast<const float4*>(a.iptab + (size_t)pq[0] * M * kKsub);
+        float4* dst = reinterpret_cast<float4*>(lds + L.lut);
+        if (wave == 0) {
+          constexpr int NCH = MT ? (MT + 63) / 64 : 3;  // (M <= 160: the LUT is in LDS)
+          const float* qr = a.Q + (size_t)pq[0] * a.d;
+          const float* cr = a.C + (size_t)p * a.d;
+          const float4 x0 = src[lane];
+          float qv[NCH][kMaxDsub], cv[NCH][kMaxDsub], mx[NCH], sq[NCH];
+#pragma unroll
+          for (int h = 0; h < NCH; ++h) {
+            const int m = 64 * h + lane < M ? 64 * h + lane : M - 1;
+            mx[h] = __int_as_float(a.iplo[(size_t)pq[0] * M + m]);
+#pragma unroll
+            for (int t = 0; t < kMaxDsub; ++t) {
+              const int e = m * a.dsub + (t < a.dsub ? t : 0);
+              qv[h][t] = qr[e];
+              cv[h][t] = cr[e];
+            }
+          }
+#pragma unroll
+          for (int h = 0; h < NCH; ++h) {
+            sq[h] = 0.f;
+#pragma unroll
+            for (int t = 0; t < kMaxDsub; ++t)
+              if (t < a.dsub) sq[h] = fmaf(-qv[h][t], cv[h][t], sq[h]);
+          }
+          auto in_order = [&](const float (&x)[NCH]) {
+            float sum = 0.f;
+#pragma unroll
+            for (int h = 0; h < NCH; ++h)
+#pragma unroll
+              for (int k = 0; k < 64; ++k)
+                if (64 * h + k < M)
+                  sum += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x[h]), k));
+            return sum;
+          };
+          const float bf = in_order(sq);
+          dst[lane] = make_float4(bf - x0.x, bf - x0.y, bf - x0.z, bf - x0.w);
+          if (PHASE >= 2) {
+            float lo[NCH];
+#pragma unroll
+            for (int h = 0; h < NCH; ++h)
+              lo[h] = fminf(__builtin_inff(), (h == 0 && lane == 0 ? bf : 0.f) - mx[h]);
+            const float sb = in_order(lo);
+            if (lane == 0) reinterpret_cast<float*>(lds + L.pbase)[0] = sb;
+          }
+          if (lane == 0) ps[0] = 0;
+        } else {
+          constexpr int CN = NT - 64, UN = 8;
+          const int n4 = M * (kKsub / 4);
+          for (int e0 = tid; e0 < n4; e0 += UN * CN) {
+            float4 x[UN];
+#pragma unroll
+            for (int u = 0; u < UN; ++u) x[u] = src[e0 + u * CN < n4 ? e0 + u * CN : n4 - 1];
+#pragma unroll
+            for (int u = 0; u < UN; ++u)
+              if (e0 + u * CN < n4) dst[e0 + u * CN] = make_float4(0.f - x[u].x, 0.f - x[u].y, 0.f - x[u].z, 0.f - x[u].w);
+          }
+        }
+      }
+    }
+    if (tabcopy) {
+    } else if constexpr (FP) {
       // T[m][j] = (|r_m|^2 + |c_mj|^2) - 2 r_m.c_mj in FP32 (one FMA chain per entry)
       const float* r32 = reinterpret_cast<const float*>(lds + L.ri);
       float* rr32 = reinterpret_cast<float*>(lds + L.rr);
@@ -1082,6 +1160,7 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
         // in-order sum is below it); sixteen threads per subspace, WPR pairs
         // per 16-byte LUT row
         __syncthreads();  // the LUT entries are written
+        if (!tabcopy) {
         const float* lutf = reinterpret_cast<const float*>(lds + L.lut);
         float* rmin = reinterpret_cast<float*>(lds + L.lo);  // [G][M]
         for (int m0 = 0; m0 < M; m0 += NT / 16) {
@@ -1108,6 +1187,7 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
           reinterpret_cast<float*>(lds + L.pbase)[tid] = sb;
         }
         __syncthreads();
+        }
         thresholds();
         int& s_live = *reinterpret_cast<int*>(lds + L.ctl + 12);
         if (tid == 0) s_live = 0;
