@@ -1458,8 +1458,13 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
         const int q = pq[g];
         const int kq = a.kq ? a.kq[q] : a.kconst;
         const int kk = kq < 64 ? kq : 64;
+        // (from the highest bit a sum of the class has: phase 1 of 10000 queries
+        // of 128 dimensions 110 -> 104 us against 32 steps; ending at the first
+        // t with exactly kw minima below it 118: the steps no longer overlap)
+        constexpr int kTop = FP || LWB == 32 || H16 ? 31 : (NIB || B8 ? 14 : LWB - 1);
         uint32_t x = 0;
-        for (int bit = 31; bit >= 0; --bit) {
+#pragma unroll
+        for (int bit = kTop; bit >= 0; --bit) {
           const uint32_t t = x | (1u << bit);
           if (__popcll(__ballot(v < t)) < kk) x = t;
         }
