@@ -508,7 +508,7 @@ __global__ __launch_bounds__(256) void k_topn(const float* __restrict__ D, int n
 // order key x is found bit by bit, from the highest bit in which the row's keys
 // differ to the first candidate with exactly nprobe keys below it (distances of
 // like size share their exponents, and the candidates separate long before the
-// last bit; always 32 steps before: 1 query over 1024 lists 7.6 -> 5.4 us, 2500
+// last bit; always 32 steps before: 1 query over 1024 lists 7.6 -> 5.4 us, 4096
 // over 4096 79 -> 60, 4096 over 2048 42 -> 39; a wave per query, 10000 over 1024,
 // 37 -> 30): the count of keys below a candidate is
 // the sum over the four waves of ballot bit counts, exchanged through LDS

@@ -60,21 +60,28 @@ struct Batch {  // one in-flight search and its staging set
 };
 
 struct Staging {  // execution slot of an in-flight batch
-  void* hq = nullptr;        // pinned [cap][d] query rows
-  int32_t* hsz = nullptr;    // pinned [2][cap] per-query k, nprobe
-  int64_t* hids = nullptr;   // pinned [cap][max_k]
-  float* hdist = nullptr;
-  int64_t* hqd = nullptr;
-  int32_t* hstatus = nullptr;  // pinned: device status of the batch's search
-  void* dq = nullptr;        // device copies
-  int32_t* dsz = nullptr;
-  int64_t* dids = nullptr;
-  float* ddist = nullptr;
-  int64_t* dqd = nullptr;
-  int32_t* dstatus = nullptr;
+  // one block each way, pinned and on the device, laid out for the batch's
+  // bucket nb so that a batch is one upload and one download (two uploads and
+  // four downloads on the slot's stream before: a burst of 300 requests, d 768,
+  // 1.21 -> 1.12 ms, means of four and three runs that differ by up to 0.2 ms
+  // with the sizes of the batches the worker happens to form)
+  char* hin = nullptr;       // [nb][d] query rows, [2][nb] per-query k, nprobe
+  char* din = nullptr;
+  char* hres = nullptr;      // [nb][max_k] ids, [nb][max_k] distances, status, [nb][max_k] integer distances
+  char* dres = nullptr;
   hipEvent_t ev = nullptr;   // results copied back
   hipStream_t stream = nullptr;
   Workspace ws;              // search scratch of this slot
+};
+
+// where a bucket's sizes follow its query rows, and its result arrays (64-byte
+// aligned: the kernels' stores need no more than 8)
+size_t up64(size_t x) { return (x + 63) & ~(size_t)63; }
+size_t in_sizes(size_t nb, size_t row) { return up64(nb * row); }
+struct ResLayout {
+  size_t dist, status, qdist, total;
+  ResLayout(size_t nb, size_t K)
+      : dist(up64(nb * K * 8)), status(dist + up64(nb * K * 4)), qdist(status + 64), total(qdist + nb * K * 8) {}
 };
 
 // batch size bucket (graphs are captured per bucket): powers of two up to
@@ -130,10 +137,10 @@ amp_server::~amp_server() {
     if (s.stream) (void)hipStreamSynchronize(s.stream);
     release_workspace(s.ws);
     if (s.ev) (void)hipEventDestroy(s.ev);
-    void* host[] = {s.hq, s.hsz, s.hids, s.hdist, s.hqd, s.hstatus};
+    void* host[] = {s.hin, s.hres};
     for (void* p : host)
       if (p) (void)hipHostFree(p);
-    void* dev[] = {s.dq, s.dsz, s.dids, s.ddist, s.dqd, s.dstatus};
+    void* dev[] = {s.din, s.dres};
     for (void* p : dev)
       if (p) (void)hipFree(p);
     if (s.stream) (void)hipStreamDestroy(s.stream);
@@ -154,19 +161,12 @@ amp_status amp_server::init() {
     if (s != AMP_OK) return s;
     // default-priority streams of their own: the two slots' searches overlap
     if (hipStreamCreateWithFlags(&g.stream, hipStreamNonBlocking) != hipSuccess) return hfail("stream");
-    if (hipHostMalloc(&g.hq, B * row, hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&g.hsz), 2 * B * 4, hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&g.hids), B * K * 8, hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&g.hdist), B * K * 4, hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&g.hqd), B * K * 8, hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&g.hstatus), 4, hipHostMallocDefault) != hipSuccess)
+    const size_t in = in_sizes(B, row) + 2 * B * 4, res = ResLayout(B, K).total;
+    if (hipHostMalloc(reinterpret_cast<void**>(&g.hin), in, hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void**>(&g.hres), res, hipHostMallocDefault) != hipSuccess)
       return hfail("pinned staging");
-    std::memset(g.hq, 0, B * row);  // padded rows stay zero
-    if (hipMalloc(&g.dq, B * row) != hipSuccess || hipMalloc(reinterpret_cast<void**>(&g.dsz), 2 * B * 4) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void**>(&g.dids), B * K * 8) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void**>(&g.ddist), B * K * 4) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void**>(&g.dqd), B * K * 8) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void**>(&g.dstatus), 4) != hipSuccess)
+    if (hipMalloc(reinterpret_cast<void**>(&g.din), in) != hipSuccess ||
+        hipMalloc(reinterpret_cast<void**>(&g.dres), res) != hipSuccess)
       return hfail("device staging");
     if (hipEventCreateWithFlags(&g.ev, hipEventDisableTiming) != hipSuccess) return hfail("event");
     // the slot's search scratch, sized now for the largest batch: growing it
@@ -187,25 +187,28 @@ void amp_server::launch(Batch& b) {
   const size_t row = (size_t)d * esize;
   const int n = (int)b.reqs.size();
   const int nb = bucket_of(n);
-  int32_t* hk = s.hsz;
-  int32_t* hnp = s.hsz + cap;
+  const size_t sizes = in_sizes(nb, row);
+  const ResLayout L(nb, cfg.max_k);
+  int32_t* hk = reinterpret_cast<int32_t*>(s.hin + sizes);
+  int32_t* hnp = hk + nb;
+  bool qdist = false;
   for (int i = 0; i < n; ++i) {
     Request* r = b.reqs[i];
-    std::memcpy(static_cast<char*>(s.hq) + i * row, static_cast<char*>(pool) + (size_t)r->slot * row, row);
+    std::memcpy(s.hin + i * row, static_cast<char*>(pool) + (size_t)r->slot * row, row);
     hk[i] = r->k;
     hnp[i] = r->nprobe;
     b.kmax = std::max(b.kmax, r->k);
+    qdist |= r->out_qdist != nullptr;
   }
   // padding rows: zero queries with k = nprobe = 1 (their results are dropped)
-  std::memset(static_cast<char*>(s.hq) + (size_t)n * row, 0, (size_t)(nb - n) * row);
+  std::memset(s.hin + (size_t)n * row, 0, (size_t)(nb - n) * row);
   for (int i = n; i < nb; ++i) hk[i] = hnp[i] = 1;
   {
     std::lock_guard<std::mutex> lk(mu);  // the rows are copied: the slots take new requests
     for (Request* r : b.reqs) free_slots.push_back(r->slot);
   }
   hipError_t e;
-  if ((e = hipMemcpyAsync(s.dq, s.hq, nb * row, hipMemcpyHostToDevice, s.stream)) != hipSuccess ||
-      (e = hipMemcpyAsync(s.dsz, s.hsz, 2 * (size_t)cap * 4, hipMemcpyHostToDevice, s.stream)) != hipSuccess) {
+  if ((e = hipMemcpyAsync(s.din, s.hin, sizes + 2 * (size_t)nb * 4, hipMemcpyHostToDevice, s.stream)) != hipSuccess) {
     (void)hipGetLastError();
     b.status = set_error(AMP_EDEVICE, "server: query upload failed: %s", hipGetErrorString(e));
     return;
@@ -213,19 +216,19 @@ void amp_server::launch(Batch& b) {
   amp_search_opts o{};
   o.mem = AMP_MEM_DEVICE;
   o.stream = s.stream;
-  o.out_qdist = s.dqd;
+  o.out_qdist = reinterpret_cast<int64_t*>(s.dres + L.qdist);
   o.q_dtype = cfg.q_dtype;
   o.flags = AMP_SEARCH_GRAPH | AMP_SEARCH_DEVICE_SIZES;
   o.kmax = cfg.max_k;
   o.npmax = cfg.max_nprobe;
-  o.out_status = s.dstatus;
-  b.status = search_on(ix, s.ws, s.dq, nb, s.dsz, s.dsz + cap, 1, &b.reqs[0]->policy, &o, s.dids, s.ddist);
+  o.out_status = reinterpret_cast<int32_t*>(s.dres + L.status);
+  const int32_t* dk = reinterpret_cast<const int32_t*>(s.din + sizes);
+  b.status = search_on(ix, s.ws, s.din, nb, dk, dk + nb, 1, &b.reqs[0]->policy, &o,
+                       reinterpret_cast<int64_t*>(s.dres), reinterpret_cast<float*>(s.dres + L.dist));
   if (b.status != AMP_OK) return;
-  const size_t nk = (size_t)n * cfg.max_k;
-  if ((e = hipMemcpyAsync(s.hids, s.dids, nk * 8, hipMemcpyDeviceToHost, s.stream)) != hipSuccess ||
-      (e = hipMemcpyAsync(s.hdist, s.ddist, nk * 4, hipMemcpyDeviceToHost, s.stream)) != hipSuccess ||
-      (e = hipMemcpyAsync(s.hqd, s.dqd, nk * 8, hipMemcpyDeviceToHost, s.stream)) != hipSuccess ||
-      (e = hipMemcpyAsync(s.hstatus, s.dstatus, 4, hipMemcpyDeviceToHost, s.stream)) != hipSuccess ||
+  // (the integer distances, last, only where a request takes them)
+  if ((e = hipMemcpyAsync(s.hres, s.dres, qdist ? L.total : L.status + 4, hipMemcpyDeviceToHost, s.stream)) !=
+          hipSuccess ||
       (e = hipEventRecord(s.ev, s.stream)) != hipSuccess) {
     (void)hipGetLastError();
     b.status = set_error(AMP_EDEVICE, "server: result copy failed: %s", hipGetErrorString(e));
@@ -235,15 +238,16 @@ void amp_server::launch(Batch& b) {
 // wait for the batch, hand each request its rows, run the callbacks
 void amp_server::complete(Batch& b) {
   Staging& s = stg[b.set];
+  const ResLayout L(bucket_of((int)b.reqs.size()), cfg.max_k);
   if (b.status == AMP_OK) {
     const hipError_t e = hipEventSynchronize(s.ev);
     if (e != hipSuccess) {
       (void)hipGetLastError();
       b.status = set_error(AMP_EDEVICE, "server: batch failed: %s", hipGetErrorString(e));
-    } else if (*s.hstatus != AMP_OK) {
+    } else if (const int32_t dev_status = *reinterpret_cast<const int32_t*>(s.hres + L.status); dev_status != AMP_OK) {
       // the device reported an error (a candidate overflow): the batch fails
-      b.status = set_error(*s.hstatus, "server: the batch's search reported %s on the device",
-                           amp_status_str(*s.hstatus));
+      b.status = set_error((amp_status)dev_status, "server: the batch's search reported %s on the device",
+                           amp_status_str((amp_status)dev_status));
     }
   }
   std::vector<std::pair<Request*, amp_status>> fin;
@@ -260,9 +264,9 @@ void amp_server::complete(Batch& b) {
         ++cancelled;
       } else if (st == AMP_OK) {
         const size_t o = i * (size_t)cfg.max_k;
-        std::memcpy(r->out_ids, s.hids + o, r->k * 8);
-        std::memcpy(r->out_dist, s.hdist + o, r->k * 4);
-        if (r->out_qdist) std::memcpy(r->out_qdist, s.hqd + o, r->k * 8);
+        std::memcpy(r->out_ids, s.hres + o * 8, r->k * 8);
+        std::memcpy(r->out_dist, s.hres + L.dist + o * 4, r->k * 4);
+        if (r->out_qdist) std::memcpy(r->out_qdist, s.hres + L.qdist + o * 8, r->k * 8);
         ++completed;
         if (lat_ms.size() < kMaxLatencySamples) lat_ms.push_back((float)((t - r->arrival_ns) * 1e-6));
       } else {
