@@ -97,7 +97,9 @@ __device__ __forceinline__ int row16_reduce(int v) {
 // products are exact; the FP8 (e4m3) build puts the dimension products on
 // the FP8 MFMA, whose sums of e4m3-grid products are not always exact: its
 // entries are the rounded FP32 results.
-enum { DT_BF16 = 1, DT_F16 = 2, DT_F8 = 3 };
+// DT_TAB marks the scan kernels of the FP32 LUT (which has no matrix dtype)
+// that copy it from a query's inner-product table.
+enum { DT_BF16 = 1, DT_F16 = 2, DT_F8 = 3, DT_TAB = 4 };
 
 // four floats as OCP e4m3 bytes (the hardware conversion; exact for the
 // e4m3-representable integers of the e4m3 operand grid)

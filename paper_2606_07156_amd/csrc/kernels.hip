@@ -2586,6 +2586,7 @@ static int g_num_cu = 0;
 // AMP_SCAN_WG512=0 keeps 256).
 static hipError_t launch_scan(int lwb, int ph, int dt, int wpr, const ScanArgs& sa, hipStream_t st) {
   const bool mix = lwb < 0;
+  if (lwb == 0) dt = sa.metric == AMP_IP && wpr == 1 ? DT_TAB : DT_BF16;
   auto pick = [&](int nt) {
     return ph == 1 ? pick_scan_ph1(lwb, sa.M, dt, wpr, nt)
                    : (ph == 2 ? pick_scan_ph2(lwb, sa.M, dt, wpr, nt) : pick_scan_ph3(lwb, sa.M, dt, wpr, nt));

@@ -541,7 +541,14 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
   constexpr int W = Lane<LWB>::W;
   constexpr int G = WPR * W;
   constexpr uint32_t MASK = Lane<LWB>::MASK;
-  constexpr bool CRES = FP && MT != 0 && MT <= 16;  // FP32 codewords stay in registers
+  // FP32 inner product, one pair per unit: the LUT is copied from the query's
+  // table, without residual rows.  A kernel of its own: with the copy behind a
+  // branch on the metric, its rows in flight set the registers of every FP32
+  // scan (generic variant under L2 and L1: 126 and 16 bytes of scratch, four
+  // waves per SIMD, against 57, none and seven without it).
+  constexpr bool TAB = FP && DT == DT_TAB;
+  static_assert(!TAB || WPR == 1, "table copy: one pair per unit");
+  constexpr bool CRES = FP && !TAB && MT != 0 && MT <= 16;  // FP32 codewords stay in registers
   constexpr int MPAR = NT / kKsub;  // FP32 LUT: subspaces built side by side
   static_assert(!CRES || NT == kThreads, "FP32 codewords in registers: 256-thread workgroups");
   static_assert(NT % 64 == 0 && (NT & (NT - 1)) == 0, "NT: a power of two number of waves");
@@ -594,12 +601,9 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
     // (inner product: the query itself, on the grid for integer policies)
     // four coordinates per thread and step (d is a multiple of 4, query rows
     // and centroids 16-byte aligned); (pair, quad) advanced without division
-    const bool ip = a.metric == AMP_IP;
+    const bool ip = FP && WPR == 1 ? TAB : a.metric == AMP_IP;
     const bool l1 = a.metric == AMP_L1;
-    // FP32 inner product, one pair per unit: the LUT is copied from the
-    // query's table (below), without residual rows
-    const bool tabcopy = FP && WPR == 1 && ip;
-    if ((FP || !ip) && !tabcopy) {
+    if ((FP || !ip) && !TAB) {
       const int d4 = a.d >> 2;
       const int gstep = NT / d4, tstep = NT - gstep * d4;
       int g = tid / d4, t4 = tid - g * d4;
@@ -667,80 +671,86 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
       if (PHASE >= 2 && tid < G) pair_threshold(tid);
     };
     // ---- LC
-    if constexpr (FP && WPR == 1) {
-      // inner product, one pair per unit: entries 0 - dot, of subspace 0
-      // bf - dot with the pair's list term bf = -q.c (subspace partials added in
-      // order).  All waves but the first copy the rows of the query's table,
-      // 16 bytes a lane and eight loads ahead; the first wave meanwhile sums bf
-      // and the pair's lower bound (rows' smallest entries, from the largest dot
-      // products, in the scan's subspace order), then writes row 0.  (Entry by
-      // entry behind the residual stage, with the minima read back from the LUT,
-      // a unit of 2200 vectors took 29 us, most of it waiting for one load after
-      // another: 4021 us for 36k units, d 768, M 96; 2064 now, near what the
-      // LDS reads of the scan itself take.)
-      if (tabcopy) {
-        const float4* src = reinterpret_cast<const float4*>(a.iptab + (size_t)pq[0] * M * kKsub);
-        float4* dst = reinterpret_cast<float4*>(lds + L.lut);
-        if (wave == 0) {
-          constexpr int NCH = MT ? (MT + 63) / 64 : 3;  // (M <= 160: the LUT is in LDS)
-          const float* qr = a.Q + (size_t)pq[0] * a.d;
-          const float* cr = a.C + (size_t)p * a.d;
-          const float4 x0 = src[lane];
-          float qv[NCH][kMaxDsub], cv[NCH][kMaxDsub], mx[NCH], sq[NCH];
+    if constexpr (TAB) {
+      // entries 0 - dot, of subspace 0 bf - dot with the pair's list term
+      // bf = -q.c (subspace partials added in order).  All waves but the first
+      // copy the rows of the query's table, 16 bytes a lane and eight loads
+      // ahead; the first wave meanwhile sums bf and the pair's lower bound
+      // (rows' smallest entries, from the largest dot products, in the scan's
+      // subspace order), then writes row 0: 64 subspaces per step where M is
+      // not known, all of them at once where it is.  (Entry by entry behind the
+      // residual stage, with the minima read back from the LUT, a unit of 2200
+      // vectors took 29 us, most of it waiting for one load after another: 4021
+      // us for 36k units, d 768, M 96; 2064 now, near what the LDS reads of the
+      // scan itself take.)
+      const float4* src = reinterpret_cast<const float4*>(a.iptab + (size_t)pq[0] * M * kKsub);
+      float4* dst = reinterpret_cast<float4*>(lds + L.lut);
+      if (wave == 0) {
+        constexpr int HN = MT ? (MT + 63) / 64 : 1, STEP = 64 * HN;
+        const float* qr = a.Q + (size_t)pq[0] * a.d;
+        const float* cr = a.C + (size_t)p * a.d;
+        const float4 x0 = src[lane];
+        auto mine = [&](int h0, int h) { return h0 + 64 * h + lane < M ? h0 + 64 * h + lane : M - 1; };
+        float mx[HN];
+        auto row_max = [&](int h0) {
 #pragma unroll
-          for (int h = 0; h < NCH; ++h) {
-            const int m = 64 * h + lane < M ? 64 * h + lane : M - 1;
-            mx[h] = __int_as_float(a.iplo[(size_t)pq[0] * M + m]);
+          for (int h = 0; h < HN; ++h) mx[h] = __int_as_float(a.iplo[(size_t)pq[0] * M + mine(h0, h)]);
+        };
+        auto add_in_order = [&](float sum, int h0, const float (&x)[HN]) {
+#pragma unroll
+          for (int h = 0; h < HN; ++h)
+#pragma unroll
+            for (int k = 0; k < 64; ++k)
+              if (h0 + 64 * h + k < M) sum += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x[h]), k));
+          return sum;
+        };
+        row_max(0);
+        float bf = 0.f;
+        for (int h0 = 0; h0 < M; h0 += STEP) {
+          float qv[HN][kMaxDsub], cv[HN][kMaxDsub], sq[HN];
+#pragma unroll
+          for (int h = 0; h < HN; ++h)
 #pragma unroll
             for (int t = 0; t < kMaxDsub; ++t) {
-              const int e = m * a.dsub + (t < a.dsub ? t : 0);
+              const int e = mine(h0, h) * a.dsub + (t < a.dsub ? t : 0);
               qv[h][t] = qr[e];
               cv[h][t] = cr[e];
             }
-          }
 #pragma unroll
-          for (int h = 0; h < NCH; ++h) {
+          for (int h = 0; h < HN; ++h) {
             sq[h] = 0.f;
 #pragma unroll
             for (int t = 0; t < kMaxDsub; ++t)
               if (t < a.dsub) sq[h] = fmaf(-qv[h][t], cv[h][t], sq[h]);
           }
-          auto in_order = [&](const float (&x)[NCH]) {
-            float sum = 0.f;
+          bf = add_in_order(bf, h0, sq);
+        }
+        dst[lane] = make_float4(bf - x0.x, bf - x0.y, bf - x0.z, bf - x0.w);
+        if (PHASE >= 2) {
+          float sb = 0.f;
+          for (int h0 = 0; h0 < M; h0 += STEP) {
+            if (h0) row_max(h0);
+            float lo[HN];
 #pragma unroll
-            for (int h = 0; h < NCH; ++h)
-#pragma unroll
-              for (int k = 0; k < 64; ++k)
-                if (64 * h + k < M)
-                  sum += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x[h]), k));
-            return sum;
-          };
-          const float bf = in_order(sq);
-          dst[lane] = make_float4(bf - x0.x, bf - x0.y, bf - x0.z, bf - x0.w);
-          if (PHASE >= 2) {
-            float lo[NCH];
-#pragma unroll
-            for (int h = 0; h < NCH; ++h)
-              lo[h] = fminf(__builtin_inff(), (h == 0 && lane == 0 ? bf : 0.f) - mx[h]);
-            const float sb = in_order(lo);
-            if (lane == 0) reinterpret_cast<float*>(lds + L.pbase)[0] = sb;
+            for (int h = 0; h < HN; ++h)
+              lo[h] = fminf(__builtin_inff(), (h0 + 64 * h + lane == 0 ? bf : 0.f) - mx[h]);
+            sb = add_in_order(sb, h0, lo);
           }
-          if (lane == 0) ps[0] = 0;
-        } else {
-          constexpr int CN = NT - 64, UN = 8;
-          const int n4 = M * (kKsub / 4);
-          for (int e0 = tid; e0 < n4; e0 += UN * CN) {
-            float4 x[UN];
+          if (lane == 0) reinterpret_cast<float*>(lds + L.pbase)[0] = sb;
+        }
+        if (lane == 0) ps[0] = 0;
+      } else {
+        constexpr int CN = NT - 64, UN = 8;
+        const int n4 = M * (kKsub / 4);
+        for (int e0 = tid; e0 < n4; e0 += UN * CN) {
+          float4 x[UN];
 #pragma unroll
-            for (int u = 0; u < UN; ++u) x[u] = src[e0 + u * CN < n4 ? e0 + u * CN : n4 - 1];
+          for (int u = 0; u < UN; ++u) x[u] = src[e0 + u * CN < n4 ? e0 + u * CN : n4 - 1];
 #pragma unroll
-            for (int u = 0; u < UN; ++u)
-              if (e0 + u * CN < n4) dst[e0 + u * CN] = make_float4(0.f - x[u].x, 0.f - x[u].y, 0.f - x[u].z, 0.f - x[u].w);
-          }
+          for (int u = 0; u < UN; ++u)
+            if (e0 + u * CN < n4) dst[e0 + u * CN] = make_float4(0.f - x[u].x, 0.f - x[u].y, 0.f - x[u].z, 0.f - x[u].w);
         }
       }
-    }
-    if (tabcopy) {
     } else if constexpr (FP) {
       // T[m][j] = (|r_m|^2 + |c_mj|^2) - 2 r_m.c_mj in FP32 (one FMA chain per entry)
       const float* r32 = reinterpret_cast<const float*>(lds + L.ri);
@@ -834,7 +844,7 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
         }
       };
       if (l1) fill(std::integral_constant<int, 2>{});
-      else if (ip) fill(std::integral_constant<int, 1>{});
+      else if (WPR > 1 && ip) fill(std::integral_constant<int, 1>{});
       else fill(std::integral_constant<int, 0>{});
     } else if (ip) {
       // inner product: the LUT is the query's, quantised once per (query,
@@ -1160,7 +1170,7 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
         // in-order sum is below it); sixteen threads per subspace, WPR pairs
         // per 16-byte LUT row
         __syncthreads();  // the LUT entries are written
-        if (!tabcopy) {
+        if constexpr (!TAB) {
         const float* lutf = reinterpret_cast<const float*>(lds + L.lut);
         float* rmin = reinterpret_cast<float*>(lds + L.lo);  // [G][M]
         for (int m0 = 0; m0 < M; m0 += NT / 16) {
@@ -1507,7 +1517,7 @@ __global__ __launch_bounds__(NT, scan_min_blocks(MT, NT))
   constexpr int WPR = class_wpr(LWB, variant_wpr(MT, NR));
   constexpr bool FP = LWB == 0;
   constexpr int G = WPR * Lane<LWB>::W;
-  constexpr bool CRES = FP && MT != 0 && MT <= 16;
+  constexpr bool CRES = FP && DT != DT_TAB && MT != 0 && MT <= 16;
   constexpr int MPAR = NT / kKsub;
   static_assert(!CRES || NT == kThreads, "FP32 codewords in registers: 256-thread workgroups");
   const int M = MT ? MT : a.M;

@@ -4,12 +4,16 @@ build (a batch that fills the chip), at numbers of subspaces that a split does
 not divide.  FP32 policy: the pairs left out by the bound from the coarse
 distance change nothing, at every subspace width, at edges of the table
 kernel's groups of four and 32 queries, for data far from the origin (where the
-bound's slack is large against the distances' differences) and odd queries."""
+bound's slack is large against the distances' differences) and odd queries; the scan that copies
+its LUT from the table agrees with FP64, at every number of its steps of 64
+subspaces; so does the bound that integer cluster locating leaves to the rows
+themselves."""
 import numpy as np
 import pytest
 
 import oracle
 import paper_2606_07156_amd as amp
+from _parity import compare_fp32
 from test_gpu_pair_bounds import random_index
 
 pytestmark = pytest.mark.gpu
@@ -55,3 +59,30 @@ def test_fp32_bound_from_the_coarse_distance(monkeypatch, M, dsub, offset):
             assert np.array_equal(got[f], want[f], equal_nan=f == "dist"), (nq, f)
         dead += got["work"]["dead_pairs"]
     assert dead > 0
+
+
+@pytest.mark.parametrize("M", [12, 64, 68, 100, 128, 132, 152])
+def test_fp32_scan_of_copied_tables(M):
+    idx = random_index(M, M, 2, metric="ip", n=3000)
+    h = amp.amp_index_from_arrays(idx)
+    r = np.random.default_rng(M)
+    Q = (idx["centroids"][r.integers(1, 40, 20)] + r.standard_normal((20, idx["d"]))).astype(np.float32)
+    got = amp.amp_search(h, Q, 10, 12, policy="fp32", want_probes=True)
+    compare_fp32(got, oracle.search(idx, Q, 10, 12, policy="fp32", probes=got["probes"]), idx, Q)
+
+
+@pytest.mark.parametrize("M,dsub", [(16, 8), (36, 4), (96, 8)])
+def test_fp32_bound_under_integer_cluster_locating(monkeypatch, M, dsub):
+    idx = random_index(M + 1, M, dsub, metric="ip")
+    h = amp.amp_index_from_arrays(idx)
+    amp.amp_index_build_cl_map(h, M // 4, 8, iters=4, seed=2)
+    r = np.random.default_rng(M)
+    Q = (idx["centroids"][r.integers(0, 40, 70)] + r.standard_normal((70, idx["d"]))).astype(np.float32)
+    kw = dict(policy="fp32", cl_policy="fixed", cl_bits=8, want_probes=True)
+    got = amp.amp_search(h, Q, 5, 20, work=True, **kw)
+    monkeypatch.setenv("AMP_PAIR_SKIP", "0")
+    want = amp.amp_search(h, Q, 5, 20, **kw)
+    for f in ("ids", "dist", "probes"):
+        assert np.array_equal(got[f], want[f]), f
+    assert got["work"]["dead_pairs"] > 0
+    compare_fp32(got, oracle.search(idx, Q, 5, 20, policy="fp32", probes=got["probes"]), idx, Q)
