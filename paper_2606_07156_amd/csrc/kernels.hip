@@ -2955,7 +2955,7 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
       while (G > 8 && (size_t)G * ri_stride(sd.d) * 2 > 65536) G >>= 1;
       ba.G = G;
       const size_t blds = base_lds_layout(G, sd.M, sd.d).total;
-      auto fn = k_base<DT_F8>;  // (L1 has no MFMA dtype)
+      auto fn = sd.metric == AMP_L1 ? k_base<true> : k_base<false>;
       if ((err = set_lds(kaddr(fn), blds)) != hipSuccess)
         return err;
       hipLaunchKernelGGL(fn, dim3((unsigned)((npairs + G - 1) / G)), dim3(kThreads), blds, st, ba);

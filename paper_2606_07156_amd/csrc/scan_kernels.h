@@ -1763,9 +1763,13 @@ __device__ __forceinline__ void base_frags(const BaseArgs& b, int mp, int lane, 
 
 // L1 and the FP8 build (L2 with an exact build: k_base_l2): b.G consecutive
 // pair slots per workgroup (any queries, any
-// lists; empty slots have zero rows and write nothing).  Every m-pair's B
-// fragments, loaded once per workgroup and wave, serve all G pairs.
-template <int DT>
+// lists; empty slots have zero rows and write nothing).  FP8: every m-pair's B
+// fragments, loaded once per workgroup and wave, serve all G pairs.  L1 runs on
+// the VALU and is a kernel of its own, of 47 registers: as a branch beside the
+// FP8 build's fragments it had 376, one wave per SIMD (2000 queries, nprobe 32,
+// whole searches with the branch and without: M 8, 8 bits, 551 and 475 us; M 16,
+// 4 bits, 856 and 790).
+template <bool L1>
 __global__ __launch_bounds__(kThreads) void k_base(BaseArgs b) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int G = b.G;
@@ -1803,7 +1807,7 @@ __global__ __launch_bounds__(kThreads) void k_base(BaseArgs b) {
   __syncthreads();
   const int16_t* ri = reinterpret_cast<const int16_t*>(lds + L.ri);
   int32_t* lo = reinterpret_cast<int32_t*>(lds + L.lo);
-  if (b.metric == AMP_L1) {
+  if constexpr (L1) {
     // a thread per (pair, subspace) row: minimum over the codewords on the VALU
     for (int e = tid; e < G * M; e += kThreads) {
       const int g = e / M, m = e % M;
@@ -1834,8 +1838,8 @@ __global__ __launch_bounds__(kThreads) void k_base(BaseArgs b) {
     __syncthreads();
     for (int mp = wave; mp < M / 2; mp += kThreads / 64) {
       u32x4 Bt[16], Bd[16];
-      base_frags<DT>(b, mp, lane, Bt, Bd);
-      lut_row_minima<DT>(a, lds, L, M, G, mp, Bt, Bd);
+      base_frags<DT_F8>(b, mp, lane, Bt, Bd);
+      lut_row_minima<DT_F8>(a, lds, L, M, G, mp, Bt, Bd);
     }
   }
   __syncthreads();

@@ -1,9 +1,11 @@
-"""Registers of the FP32 scan kernels, from the metadata of the built library.
+"""Registers of the FP32 scan and L1 base kernels, from the metadata of the
+built library.
 
 Under L2 and L1 a scan kernel computes its LUT from the residuals; the copy of
 a query's inner-product table belongs to kernels of its own, so its registers
 cost these searches no wavefronts in flight.  A SIMD has 512 vector registers
-per lane, handed out in steps of 8: 72 of them leave seven waves, 96 five.
+per lane, handed out in steps of 8: 72 of them leave seven waves, 96 five.  L1's pair bases run on the VALU,
+without the matrix fragments of the other builds' bases.
 """
 import os
 import struct
@@ -54,3 +56,9 @@ def test_l2_and_l1_scans_keep_their_wavefronts(kernels, M, threads, vgprs, phase
     k = kernels[f"_ZN3amp6k_scanILi0ELi{M}ELi{phase}ELi1ELi0ELi{threads}EEEvNS_8ScanArgsE"]
     assert k[".private_segment_fixed_size"] == 0
     assert k[".vgpr_count"] <= vgprs
+
+
+def test_l1_pair_bases_keep_their_wavefronts(kernels):
+    k = kernels["_ZN3amp6k_baseILb1EEEvNS_8BaseArgsE"]
+    assert k[".private_segment_fixed_size"] == 0
+    assert k[".vgpr_count"] <= 72
