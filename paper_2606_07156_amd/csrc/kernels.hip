@@ -3090,7 +3090,7 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
     } else {
       sa.cls = -1;
       sa.counter = ws.counters + ((ph - 1) * (kNCls + 1) + kNCls) * kQueueSlot;
-      sa_lwb = -1;
+      sa_lwb = sd.gran ? kLwMixSub : kLwMix;
     }
     ScanArgs sp = sa;
     sp.work = (ph == 2 && sd.want_work) ? ws.work : nullptr;

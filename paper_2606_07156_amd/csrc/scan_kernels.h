@@ -136,6 +136,16 @@ __host__ __device__ inline ScanLds scan_lds_layout(int G, int wpr, int M, int d,
   return L;
 }
 
+// x as a value of this place.  Conditions on a kernel argument are otherwise
+// taken to the kernel's start and held over every unit: those on dsub, one per
+// dimension, in scalar registers that spill to vector lanes, which are read back
+// at each use (8-bit pairs in the mixed-class kernel, L1, M 16: 23 % more VALU
+// instructions, phase 2 513 us against 444 with a body less in the kernel).
+__device__ __forceinline__ int local_scalar(int x) {
+  asm volatile("" : "+s"(x));
+  return x;
+}
+
 template <int LWB>  // lane bits 4/8/16/32, kLwByte, kLwHalf, 0 = FP32 LUT
 struct Lane {
   static constexpr int W = lane_fields(LWB);
@@ -221,7 +231,7 @@ __device__ __forceinline__ void mpair_a_tile(const ScanArgs& a, const char* lds,
   const int32_t* ps = reinterpret_cast<const int32_t*>(lds + L.ps);
   const int row = lane & 15, kg = lane >> 4;
   const int ms_row = row >> 3;
-  const int dsub = a.dsub;
+  const int dsub = local_scalar(a.dsub);
   const int rs = ri_stride(a.d);
   const int g = gt * 8 + (row & 7);
   const int m = 2 * mp + ms_row;
@@ -386,7 +396,7 @@ __device__ __forceinline__ void lut_mpair(const ScanArgs& a, char* lds, const Sc
   uint32_t* lut = reinterpret_cast<uint32_t*>(lds + L.lut);
   const int row = lane & 15, kg = lane >> 4;
   const int ms_row = row >> 3;
-  const int dsub = a.dsub;
+  const int dsub = local_scalar(a.dsub);
   const int rs = ri_stride(a.d);
   constexpr bool ip = IP;  // metric as a compile-time flag: no per-value select
   bf16x8 A[NGT];
@@ -1041,6 +1051,7 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
       // (subspace, codeword) entry quantises it for every pair of the unit
       // and packs the row words as the MFMA build does.
       auto build_l1 = [&](int pass) {
+        const int dsub = local_scalar(a.dsub);
         int32_t* lo = reinterpret_cast<int32_t*>(lds + L.lo);
         int32_t* hi = reinterpret_cast<int32_t*>(lds + L.hi);
         if (pass == 1) {
@@ -1048,7 +1059,7 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
             const int g = e / M, m = e % M;
             int rv[kMaxDsub];
 #pragma unroll
-            for (int t = 0; t < kMaxDsub; ++t) rv[t] = t < a.dsub ? (int)ri[g * ri_stride(a.d) + m * a.dsub + t] : 0;
+            for (int t = 0; t < kMaxDsub; ++t) rv[t] = t < dsub ? (int)ri[g * ri_stride(a.d) + m * dsub + t] : 0;
             int mn = 0x7FFFFFFF, mx = 0;
             const int16_t* cb = a.cbi16 + (size_t)m * kKsub * 8;
             for (int j = 0; j < kKsub; ++j) {
@@ -1080,7 +1091,7 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
                   int v = 0;
 #pragma unroll
                   for (int t = 0; t < kMaxDsub; ++t)
-                    if (t < a.dsub) v += abs((int)ri[g * ri_stride(a.d) + m * a.dsub + t] - cv[t]);
+                    if (t < dsub) v += abs((int)ri[g * ri_stride(a.d) + m * dsub + t] - cv[t]);
                   const uint32_t qv = (uint32_t)((v + lo[g * M + m]) >> ps[g]);  // lo: hf(s) - min here
                   wds[w] |= qv << (f * Lane<LWB>::EB);
                 }
@@ -1577,8 +1588,12 @@ __global__ __launch_bounds__(NT, scan_min_blocks(MT, NT))
 // the order 32-bit, 16-bit, then 4-bit (one width per pair) or 8-bit units
 // (each largest list first): the few wide units start early and the many
 // narrow units fill the tail.  The LDS tile of the 4-bit class (the most
-// pairs per unit) serves every class.
-template <int MT, int PHASE, int DT, int NR, int NT>
+// pairs per unit) serves every class.  GRAN: quantiser granularity, whose classes
+// alone the kernel holds (three bodies; with both granularities' it took 48 bytes
+// of scratch per lane at M 24, 80 at M 120, 128 at M 128, and now none, none and
+// 48; whole searches, 2000 queries, with both / now: L1 M 16 1061 / 964 us, L2
+// M 16 183 / 172, M 40 515 / 502, inner product M 128 769 / 751).
+template <int MT, int PHASE, int DT, int NR, int NT, int GRAN>
 __global__ __launch_bounds__(NT, scan_min_blocks(MT, NT))
     __attribute__((amdgpu_waves_per_eu(NT / 64 * scan_min_blocks(MT, NT) / 4, NT == 512 ? 2 : 8))) void k_scan_mix(ScanArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -1601,7 +1616,7 @@ __global__ __launch_bounds__(NT, scan_min_blocks(MT, NT))
   // unit number in launch order -> (class, row of the class-major unit table)
   auto locate = [&](int64_t u, int& cls) -> int64_t {
     if (PHASE == 3) {  // (one pair per unit: the class is its width's)
-      cls = pair_class(a.pbits[a.sorted[a.units[u].y]], M, a.gran);
+      cls = pair_class(a.pbits[a.sorted[a.units[u].y]], M, GRAN);
       return u;
     }
     if (u < n2) { cls = 2; return uo[2 * (size_t)a.nlist] + u; }
@@ -1632,13 +1647,20 @@ __global__ __launch_bounds__(NT, scan_min_blocks(MT, NT))
       if (tid == 0 && next_u < total) next_unit = a.units[locate(next_u, next_cls)];
     };
     const int cls = s_cls;
-    const int lwb = lane_bits(cls, a.gran, M);
-    if (lwb == 4) scan_unit<4, MT, PHASE, DT, NR, NT>(a, lds, L, own, s_unit, fetch);
-    else if (lwb == 8) scan_unit<8, MT, PHASE, DT, NR, NT>(a, lds, L, own, s_unit, fetch);
-    else if (lwb == 16) scan_unit<16, MT, PHASE, DT, NR, NT>(a, lds, L, own, s_unit, fetch);
-    else if (lwb == kLwHalf) scan_unit<kLwHalf, MT, PHASE, DT, NR, NT>(a, lds, L, own, s_unit, fetch);
-    else if (lwb == 32) scan_unit<32, MT, PHASE, DT, NR, NT>(a, lds, L, own, s_unit, fetch);
-    else if constexpr (MT == 0 || byte_class(MT)) scan_unit<kLwByte, MT, PHASE, DT, NR, NT>(a, lds, L, own, s_unit, fetch);
+    const int lwb = lane_bits(cls, GRAN, M);
+    if constexpr (GRAN) {
+      if (lwb == 8) scan_unit<8, MT, PHASE, DT, NR, NT>(a, lds, L, own, s_unit, fetch);
+      else if (lwb == 16) scan_unit<16, MT, PHASE, DT, NR, NT>(a, lds, L, own, s_unit, fetch);
+      else scan_unit<32, MT, PHASE, DT, NR, NT>(a, lds, L, own, s_unit, fetch);
+    } else if (lwb == 4) {
+      scan_unit<4, MT, PHASE, DT, NR, NT>(a, lds, L, own, s_unit, fetch);
+    } else if (lwb == kLwHalf) {
+      scan_unit<kLwHalf, MT, PHASE, DT, NR, NT>(a, lds, L, own, s_unit, fetch);
+    } else if (MT == 0 ? lwb == kLwByte : byte_class(MT)) {
+      if constexpr (MT == 0 || byte_class(MT)) scan_unit<kLwByte, MT, PHASE, DT, NR, NT>(a, lds, L, own, s_unit, fetch);
+    } else {
+      if constexpr (!byte_class(MT)) scan_unit<16, MT, PHASE, DT, NR, NT>(a, lds, L, own, s_unit, fetch);
+    }
     __syncthreads();
     if (tid == 0) {
       s_u = next_u;
@@ -1681,7 +1703,9 @@ inline int scan_nr(int mt, int wpr) { return (wpr == 1 && kernel_wpr(mt) != 1) ?
 
 typedef void (*ScanFn)(ScanArgs);
 // the kernel of a lane class (lwb 0 = FP32 LUT, 8/16/32) or, with lwb < 0,
-// the mixed-class kernel, for one phase; nullptr if none fits
+// the mixed-class kernel (kLwMix: one width per pair, kLwMixSub: per-subspace
+// widths, whose classes are others), for one phase; nullptr if none fits
+constexpr int kLwMix = -1, kLwMixSub = -2;
 ScanFn pick_scan_ph1(int lwb, int M, int dt, int wpr, int nt);
 ScanFn pick_scan_ph2(int lwb, int M, int dt, int wpr, int nt);
 ScanFn pick_scan_ph3(int lwb, int M, int dt, int wpr, int nt);

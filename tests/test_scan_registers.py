@@ -1,11 +1,13 @@
-"""Registers of the FP32 scan and L1 base kernels, from the metadata of the
-built library.
+"""Registers of the scan and L1 base kernels, from the metadata of the built
+library.
 
 Under L2 and L1 a scan kernel computes its LUT from the residuals; the copy of
 a query's inner-product table belongs to kernels of its own, so its registers
 cost these searches no wavefronts in flight.  A SIMD has 512 vector registers
 per lane, handed out in steps of 8: 72 of them leave seven waves, 96 five.  L1's pair bases run on the VALU,
-without the matrix fragments of the other builds' bases.
+without the matrix fragments of the other builds' bases.  The mixed-class scans
+hold the widest of their lane classes' bodies without, or nearly without,
+scratch memory.
 """
 import os
 import struct
@@ -62,3 +64,11 @@ def test_l1_pair_bases_keep_their_wavefronts(kernels):
     k = kernels["_ZN3amp6k_baseILb1EEEvNS_8BaseArgsE"]
     assert k[".private_segment_fixed_size"] == 0
     assert k[".vgpr_count"] <= 72
+
+
+def test_mixed_class_scans_stay_out_of_scratch(kernels):
+    # (M 128 and one-word rows of M 24: a few registers over their waves' share)
+    mix = {n: k[".private_segment_fixed_size"] for n, k in kernels.items() if "k_scan_mix" in n}
+    assert len(mix) >= 3 * 2 * 16  # phases, granularities, shapes
+    few = {"k_scan_mixILi128E": 56, "k_scan_mixILi24E": 20}
+    assert not {n: b for n, b in mix.items() if b > max(v * (m in n) for m, v in few.items())}
