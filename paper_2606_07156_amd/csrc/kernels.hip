@@ -2584,7 +2584,8 @@ static int g_num_cu = 0;
 // per SIMD to hide the LDS and code-load latencies: the generic variant then
 // runs 512-thread workgroups (two waves per SIMD on the same LUT;
 // AMP_SCAN_WG512=0 keeps 256).
-static hipError_t launch_scan(int lwb, int ph, int dt, int wpr, const ScanArgs& sa, hipStream_t st) {
+static hipError_t launch_scan(int lwb, int ph, int dt, int wpr, const ScanArgs& sa, int64_t max_units,
+                              hipStream_t st) {
   const bool mix = lwb < 0;
   if (lwb == 0) dt = sa.metric == AMP_IP && wpr == 1 ? DT_TAB : DT_BF16;
   auto pick = [&](int nt) {
@@ -2629,8 +2630,13 @@ static hipError_t launch_scan(int lwb, int ph, int dt, int wpr, const ScanArgs& 
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&g_num_cu, hipDeviceAttributeMultiprocessorCount, dev);
   }
-  // phase 3 (the re-run) usually has nothing to do: one workgroup per CU
-  hipLaunchKernelGGL(fn, dim3(g_num_cu * (ph == 3 ? 1 : per_cu)), dim3(nt), lds, st, sa);
+  // phase 3 (the re-run) usually has nothing to do: one workgroup per CU.  No
+  // more workgroups than units: each claims from one counter before it finds
+  // the queue drained (8 queries, nprobe 32, copied FP32 LUT of M 8: phases 1 and 2
+  // in 22.8 and 26.9 us with the 2048 workgroups that fit the chip, in 9.4 and
+  // 12.6 with 256, the pairs)
+  const int64_t wgs = (int64_t)g_num_cu * (ph == 3 ? 1 : per_cu);
+  hipLaunchKernelGGL(fn, dim3((unsigned)std::max<int64_t>(1, std::min(wgs, max_units))), dim3(nt), lds, st, sa);
   return hipGetLastError();
 }
 
@@ -3094,7 +3100,9 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
     }
     ScanArgs sp = sa;
     sp.work = (ph == 2 && sd.want_work) ? ws.work : nullptr;
-    if ((err = launch_scan(sa_lwb, ph, dt, sd.wpr, sp, st)) != hipSuccess) return err;
+    // (units of one pair and list chunk at the most)
+    const int64_t most = (int64_t)npairs * ((ix->max_list + sa.chunk - 1) / sa.chunk);
+    if ((err = launch_scan(sa_lwb, ph, dt, sd.wpr, sp, most, st)) != hipSuccess) return err;
     if (ph == 1) {
       // phase-1 minima -> per-query bound, buffer emptied for the candidates
       if (small_b) {
@@ -3138,7 +3146,7 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
         sr.nrerun = ra.nrerun = ws.flags + 1 + rr;  // a unit count per round
         hipLaunchKernelGGL(k_retry, dim3(sd.nq < 256 ? sd.nq : 256), dim3(256), rlds, st, ra, qr);
         // phase 3: the phase-2 scan's re-run (its own kernel symbol)
-        if ((err = launch_scan(sa_lwb, 3, dt, sd.wpr, sr, st)) != hipSuccess) return err;
+        if ((err = launch_scan(sa_lwb, 3, dt, sd.wpr, sr, most, st)) != hipSuccess) return err;
       }
     }
   }
