@@ -1103,12 +1103,65 @@ __device__ __forceinline__ uint2 block_exclusive2(uint32_t a, uint32_t b, uint2*
 // buckets of a thread's run (odd: the runs start in distinct LDS banks)
 __host__ __device__ __forceinline__ int bucket_run(int NB, int threads) { return ((NB + threads - 1) / threads) | 1; }
 
+// exclusive sum of a 64-bit count over a workgroup of 1024 threads; s_w: 16
+// words of LDS of its own
+__device__ __forceinline__ int64_t block_exclusive64(int64_t v, int64_t* s_w, int64_t* total) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  int64_t inc = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int64_t x = __shfl_up(inc, o);
+    if (lane >= o) inc += x;
+  }
+  if (lane == 63) s_w[wv] = inc;
+  __syncthreads();
+  // (every wave scans the totals: sixteen lanes, no second barrier and, the
+  // kernel's sixteen waves being one workgroup, few registers)
+  int64_t t = s_w[lane & 15];
+#pragma unroll
+  for (int o = 1; o < 16; o <<= 1) {
+    const int64_t x = __shfl_up(t, o, 16);
+    if ((lane & 15) >= o) t += x;
+  }
+  *total = __shfl(t, 15);
+  const int64_t below = __shfl(t, wv ? wv - 1 : 0);
+  return (wv ? below : 0) + inc - v;
+}
+
+// k_qscan for up to kFewBuckets buckets, where a thread's run is at most 32
+// bytes: its counts straight into registers, one barrier per scan (900, 1536,
+// 3072 and 4095 buckets 5.4, 6.0, 7.5 and 9.1 us through LDS, 4.5, 4.6, 5.1 and
+// 6.0 this way).  33 registers: beside another stream's persistent scan a CU has
+// little room for a workgroup of sixteen waves (with 92 the kernel was as fast
+// alone, but searches on three streams became 2 to 3 % slower).
+constexpr int kFewPer = 4, kFewBuckets = kFewPer * 1024;
+__global__ __launch_bounds__(1024) void k_qscan_few(QueueArgs a) {
+  __shared__ int64_t s_w[2][16];
+  const int NB = a.ncls * a.nlist, per = (NB + 1023) / 1024, b0 = threadIdx.x * per;
+#pragma unroll 1
+  for (int i = 2 * a.ph0; i < 2 * a.ph1; ++i) {  // pair and unit counts of each phase
+    int64_t* arr = (i & 1 ? a.unitoff : a.pairoff) + (size_t)(i >> 1) * (NB + 1) + b0;
+    int64_t c[kFewPer], sum = 0, total;
+#pragma unroll
+    for (int u = 0; u < kFewPer; ++u) c[u] = u < per && b0 + u < NB ? arr[u] : 0;
+#pragma unroll
+    for (int u = 0; u < kFewPer; ++u) sum += c[u];
+    int64_t x = block_exclusive64(sum, s_w[i & 1], &total);
+#pragma unroll
+    for (int u = 0; u < kFewPer; ++u) {
+      if (u < per && b0 + u < NB) arr[u] = x;
+      x += c[u];
+    }
+    if (threadIdx.x == 0) arr[NB] = total;
+  }
+}
+
 // exclusive scans of the pair and unit counts in launch order, one workgroup
 // of 1024 threads: the counts come in coalesced and are scanned in LDS, each
 // thread a contiguous run.  (Runs read straight from memory took a cache line
 // per lane: 35 us for 12288 buckets, 13 this way.)  A bucket's units are held
 // in 32 bits, saturated: beyond any unit table.
-__global__ __launch_bounds__(1024) void k_qscan(QueueArgs a, int fp32) {
+__global__ __launch_bounds__(1024) void k_qscan(QueueArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   uint32_t* v = reinterpret_cast<uint32_t*>(lds);  // [NB]
   __shared__ int64_t s_base[1024], s_w[16];
@@ -3023,10 +3076,14 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
     }
     hipLaunchKernelGGL(k_qhist, dim3(qb), dim3(256), 0, st, q);
     hipLaunchKernelGGL(k_qtot, dim3(((ph1 - ph0) * NB + 255) / 256), dim3(256), 0, st, q, fp32 ? 1 : 0);
-    const size_t slds = (size_t)NB * 4;
-    const hipError_t e = set_lds(kaddr(k_qscan), slds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_qscan, dim3(1), dim3(1024), slds, st, q, fp32 ? 1 : 0);
+    if (NB <= kFewBuckets) {
+      hipLaunchKernelGGL(k_qscan_few, dim3(1), dim3(1024), 0, st, q);
+    } else {
+      const size_t slds = (size_t)NB * 4;
+      const hipError_t e = set_lds(kaddr(k_qscan), slds);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL(k_qscan, dim3(1), dim3(1024), slds, st, q);
+    }
     hipLaunchKernelGGL(k_qscatter, dim3(qb), dim3(256), 0, st, q);
     hipLaunchKernelGGL(k_qunits, dim3(512), dim3(256), 0, st, q, fp32 ? 1 : 0);
     return hipGetLastError();

@@ -64,3 +64,18 @@ def test_device_sizes_are_clamped_by_one_or_many_workgroups(nq):
         assert int(out["status"]) == status
         assert np.array_equal(out["ids"].cpu().numpy(), want["ids"])
         assert np.array_equal(out["dist"].cpu().numpy(), want["dist"])
+
+
+# buckets of the general queue (FP32 policy: one per list) around those that its
+# scan holds in registers, one to four per thread, and beyond
+@pytest.mark.parametrize("nlist", [100, 1023, 1024, 1025, 3073, 4096, 4097])
+def test_general_queue_at_edges_of_its_scan(nlist):
+    idx = random_index(nlist, 8, 4, nlist=nlist, n=20_000)
+    h = amp.amp_index_from_arrays(idx)
+    r = np.random.default_rng(nlist)
+    Q = (idx["centroids"][r.integers(0, nlist, 600)] + r.standard_normal((600, 32))).astype(np.float32)
+    want = amp.amp_search(h, Q, 10, 8, policy="fp32")  # 4800 pairs
+    for a in (0, 299, 500):
+        got = amp.amp_search(h, Q[a:a + 100], 10, 8, policy="fp32")  # the small queue
+        for f in ("ids", "dist"):
+            assert np.array_equal(got[f], want[f][a:a + 100]), (a, f)
