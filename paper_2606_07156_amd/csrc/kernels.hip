@@ -2835,9 +2835,12 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
   // over 1024 lists 13.7 against 7.8 us; whole searches 102 against 96 us for
   // one query, 260 / 252 for 1024, 294 / 287 for 2048, 368 / 367 for 4096, 575 /
   // 580 for 10000; over 256 lists they are even at 256 to 1024 queries and 241 /
-  // 249 at 4096)
-  constexpr int kTopnWg = 2048;
-  if (sd.npmax <= 64 && sd.nlist <= 1024 && (sd.nq > kTopnWg || sd.nlist <= 256)) {
+  // 249 at 4096.  Workgroups take four times the waves, which counts beside
+  // another stream's search: 2000 queries on three streams, 300 lists 122.7 / 123.8
+  // us, 512 lists 143.3 / 144.9 and, FP32 under L1, 821 / 857, 1024 lists 204.6 /
+  // 203.9; 1000 queries even, 300 queries over 512 lists 74.4 / 73.9)
+  const int topn_wg = sd.nlist > 512 ? 2048 : 1024;
+  if (sd.npmax <= 64 && sd.nlist <= 1024 && (sd.nq > topn_wg || sd.nlist <= 256)) {
     const dim3 g((sd.nq + 3) / 4), b(256);
     const int32_t* npq = ws.npq ? ws.npq : nullptr;
     if (sd.nlist <= 64)
