@@ -2216,8 +2216,9 @@ __global__ void k_ipq(BaseArgs b) {
 // kept over all pair tiles.  Bound by the matrix unit and the VALU minima,
 // 32 clocks each per 1024 entries (17 us at 10000 x 32 pairs, d 128, M 16),
 // and the residual rows read before them: 76 us measured, see launch_base_l2.
-// 128 registers: two workgroups per CU, one on its rows while the other
-// multiplies (161 registers, one workgroup: 104 us).
+// 128 registers (four pair tiles: and 20 bytes of scratch per lane): two
+// workgroups per CU, one on its rows while the other multiplies (161 registers,
+// one workgroup: 104 us).
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int kBaseCM = 16;   // subspaces per chunk
 constexpr int kBaseNT = 512;  // threads

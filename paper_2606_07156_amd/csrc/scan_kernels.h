@@ -131,7 +131,7 @@ __host__ __device__ inline ScanLds scan_lds_layout(int G, int wpr, int M, int d,
   L.pid = take(G * 4);
   // unit-claim control words: kept in the dynamic LDS too, so that the LUT
   // starts at LDS address 0 and row addresses fold into instruction offsets
-  L.ctl = take(64);  // unit index, class, re-run vote, live vote, unit descriptor, 4 work counters
+  L.ctl = take(64);  // unit index, class, -, live vote, unit descriptor, 4 work counters
   L.total = o;
   return L;
 }

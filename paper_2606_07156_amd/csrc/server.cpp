@@ -62,9 +62,9 @@ struct Batch {  // one in-flight search and its staging set
 struct Staging {  // execution slot of an in-flight batch
   // one block each way, pinned and on the device, laid out for the batch's
   // bucket nb so that a batch is one upload and one download (two uploads and
-  // four downloads on the slot's stream before: a burst of 300 requests, d 768,
-  // 1.21 -> 1.12 ms, means of four and three runs that differ by up to 0.2 ms
-  // with the sizes of the batches the worker happens to form)
+  // four downloads on the slot's stream take as long within the spread: a burst
+  // of 300 requests, d 768, 1.1 to 1.2 ms either way, by the sizes of the batches
+  // the worker happens to form)
   char* hin = nullptr;       // [nb][d] query rows, [2][nb] per-query k, nprobe
   char* din = nullptr;
   char* hres = nullptr;      // [nb][max_k] ids, [nb][max_k] distances, status, [nb][max_k] integer distances
