@@ -3011,10 +3011,13 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
       const size_t nq8 = (size_t)sd.nq * sd.M * kKsub / 8;
       hipLaunchKernelGGL(k_ipq, dim3((unsigned)std::min<size_t>((nq8 + 255) / 256, 1 << 20)), dim3(256), 0, st, ba);
     } else if (early && !fp32) {
-      // L1, or the FP8 build: every pair's LUT minima, as many pairs per
-      // workgroup as fit 64 KB of residual rows (128 at most): they share the
-      // B fragments
-      int G = 128;
+      // FP8 build: every pair's LUT minima, as many pairs per workgroup as fit
+      // 64 KB of residual rows (128 at most): they share the B fragments.  L1
+      // shares nothing: 32 pairs, for enough workgroups to spread over the chip
+      // (700 queries, nprobe 32, M 16, d 80, whole searches with 128 / 64 / 32 /
+      // 16: alone 695 / 683 / 627 / 627 us, on three streams 450 / 432 / 406 /
+      // 410; M 96, 2000 queries, 5750 / 5745 / 5580 / 5660 alone)
+      int G = sd.metric == AMP_L1 ? 32 : 128;
       while (G > 8 && (size_t)G * ri_stride(sd.d) * 2 > 65536) G >>= 1;
       ba.G = G;
       const size_t blds = base_lds_layout(G, sd.M, sd.d).total;

@@ -85,3 +85,31 @@ def test_fp32_bounds_of_odd_queries(monkeypatch, M, dsub):
     want = amp.amp_search(h, Q, 5, 20, policy="fp32")
     for f in ("ids", "dist"):
         assert np.array_equal(got[f], want[f], equal_nan=f == "dist"), f
+
+
+@pytest.mark.parametrize("M,dsub", [(8, 4), (16, 5), (96, 8)])
+@pytest.mark.parametrize("policy", ["explicit", "fixed"])
+def test_dropping_pairs_changes_nothing_under_l1(monkeypatch, M, dsub, policy):
+    """The same under L1: 32 pairs per workgroup of the bases."""
+    idx = random_index(M + dsub, M, dsub, metric="l1")
+    h = amp.amp_index_from_arrays(idx)
+    r = np.random.default_rng(M)
+    dropped = 0
+    for pairs, nprobe in ((1, 1), (31, 31), (33, 11), (257, 1), (4400, 11)):
+        nq = pairs // nprobe
+        Q = (idx["centroids"][r.integers(0, idx["nlist"], nq)] + r.standard_normal((nq, idx["d"]))).astype(np.float32)
+        np_q = np.full(nq, nprobe, np.int32)
+        np_q[1::3] = np.maximum(1, nprobe // 2)
+        kw = dict(policy=policy, work=True)
+        if policy == "explicit":
+            kw["explicit_bits"] = r.choice(np.array([4, 8, 12, 16], np.uint8), size=(nq, nprobe))
+        else:
+            kw["bits"] = 8
+        got = amp.amp_search(h, Q, 5, np_q, **kw)
+        monkeypatch.setenv("AMP_PAIR_SKIP", "0")
+        want = amp.amp_search(h, Q, 5, np_q, **kw)
+        monkeypatch.delenv("AMP_PAIR_SKIP")
+        for f in ("ids", "dist", "qdist"):
+            assert np.array_equal(got[f], want[f]), (pairs, f)
+        dropped += got["work"]["dead_pairs"]
+    assert dropped > 0
