@@ -1981,7 +1981,9 @@ template <int DS>  // dsub
 __global__ __launch_bounds__(256) void k_iptab_f32(BaseArgs b) {
   __shared__ float s_mx[kTabF][4];
   const int m = blockIdx.x, j = threadIdx.x, lane = j & 63;
-  const int q0 = blockIdx.y * kTabF, nqb = b.nq - q0 < kTabF ? b.nq - q0 : kTabF;
+  const int q0 = (blockIdx.z * gridDim.y + blockIdx.y) * kTabF;
+  if (q0 >= b.nq) return;
+  const int nqb = b.nq - q0 < kTabF ? b.nq - q0 : kTabF;
   float c[DS];
 #pragma unroll
   for (int t = 0; t < DS; ++t) c[t] = b.codebook[((size_t)m * kKsub + j) * DS + t];
@@ -2988,7 +2990,11 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
                                                             k_iptab_f32<4>, k_iptab_f32<5>, k_iptab_f32<6>,
                                                             k_iptab_f32<7>, k_iptab_f32<8>};
       const auto tab = kTab[sd.dsub - 1];
-      hipLaunchKernelGGL(tab, dim3((unsigned)sd.M, (unsigned)((sd.nq + kTabF - 1) / kTabF)), dim3(256), 0, st, ba);
+      // (y ends at 65535 workgroups, 2.1M queries; subspaces on x, so that
+      // neighbouring workgroups write neighbouring rows: 1024 queries, d 768, M 96,
+      // 35.8 us, with the query groups on x 37.4)
+      const unsigned tg = (unsigned)((sd.nq + kTabF - 1) / kTabF), tz = (tg + 65534) / 65535;
+      hipLaunchKernelGGL(tab, dim3((unsigned)sd.M, (tg + tz - 1) / tz, tz), dim3(256), 0, st, ba);
       if (sd.cl_policy == AMP_CL_FP32)
         hipLaunchKernelGGL(k_ipbound_f32, dim3((unsigned)sd.nq), dim3(256), 0, st, ba, coarse, ws.qnorm, dv.cnorm,
                            sd.nlist);

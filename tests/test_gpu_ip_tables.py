@@ -86,3 +86,18 @@ def test_fp32_bound_under_integer_cluster_locating(monkeypatch, M, dsub):
         assert np.array_equal(got[f], want[f]), f
     assert got["work"]["dead_pairs"] > 0
     compare_fp32(got, oracle.search(idx, Q, 5, 20, policy="fp32", probes=got["probes"]), idx, Q)
+
+
+def test_fp32_tables_beyond_the_y_limit_of_a_grid(monkeypatch):
+    """65535 groups of 32 queries, which is as many workgroups as y may have, and
+    one group more."""
+    monkeypatch.setenv("AMP_CAPQ", "64")
+    idx = random_index(3, 12, 1, nlist=8, n=200, metric="ip")
+    h = amp.amp_index_from_arrays(idx)
+    last = 65535 * 32
+    Q = np.random.default_rng(3).standard_normal((last + 5, 12)).astype(np.float32)
+    got = amp.amp_search(h, Q, 5, 2, policy="fp32")
+    for at in (slice(0, 40), slice(last - 35, last + 5)):
+        want = amp.amp_search(h, Q[at], 5, 2, policy="fp32")
+        for f in ("ids", "dist"):
+            assert np.array_equal(got[f][at], want[f]), (at, f)
