@@ -1046,31 +1046,41 @@ __device__ __forceinline__ void scan_unit(const ScanArgs& a, char* lds, const Sc
       using P2 = std::integral_constant<int, 2>;
       using L2t = std::integral_constant<bool, false>;
       // L1: T[m][j] = sum_t |ri_t - cbi_t| on the VALU (not a product, no
-      // MFMA), exact integers.  Pass 1: a thread per (pair, subspace) row
-      // finds its min / max over the 256 codewords; pass 2: a thread per
+      // MFMA), exact integers.  Pass 1: sixteen lanes per (pair, subspace) row
+      // find its min / max over the 256 codewords; pass 2: a thread per
       // (subspace, codeword) entry quantises it for every pair of the unit
       // and packs the row words as the MFMA build does.
+      // (A thread per row left most of a workgroup idle in units of few pairs, the
+      // more so with byte and 16-bit entries, which make half as many units of
+      // twice the pairs: 2000 queries, nprobe 32, d 64, adaptive, M 16, 929 us
+      // against 904 with entries as wide as the sums, 858 with sixteen lanes; 16
+      // queries over 64 lists, M 8, 175 and 124.)
       auto build_l1 = [&](int pass) {
         const int dsub = local_scalar(a.dsub);
         int32_t* lo = reinterpret_cast<int32_t*>(lds + L.lo);
         int32_t* hi = reinterpret_cast<int32_t*>(lds + L.hi);
         if (pass == 1) {
-          for (int e = tid; e < np_u * M; e += NT) {
+          for (int e = tid >> 4; e < np_u * M; e += NT / 16) {
             const int g = e / M, m = e % M;
             int rv[kMaxDsub];
 #pragma unroll
             for (int t = 0; t < kMaxDsub; ++t) rv[t] = t < dsub ? (int)ri[g * ri_stride(a.d) + m * dsub + t] : 0;
             int mn = 0x7FFFFFFF, mx = 0;
             const int16_t* cb = a.cbi16 + (size_t)m * kKsub * 8;
-            for (int j = 0; j < kKsub; ++j) {
+#pragma unroll 4
+            for (int j = tid & 15; j < kKsub; j += 16) {
               int v = 0;
 #pragma unroll
               for (int t = 0; t < kMaxDsub; ++t) v += abs(rv[t] - (int)cb[j * 8 + t]);
               mn = v < mn ? v : mn;
               mx = v > mx ? v : mx;
             }
-            lo[e] = mn;
-            hi[e] = mx;
+            mn = row16_reduce<false>(mn);  // (in the row's last lane)
+            mx = row16_reduce<true>(mx);
+            if ((tid & 15) == 15) {
+              lo[e] = mn;
+              hi[e] = mx;
+            }
           }
         } else {
           uint32_t* lut = reinterpret_cast<uint32_t*>(lds + L.lut);

@@ -37,3 +37,20 @@ def test_lane_classes_are_bit_exact(metric, M, bits):
             kw = dict(policy="explicit", explicit_bits=r.choice(np.array([4, 8, 12, 16], np.uint8), size=(nq, nprobe)))
         g = amp.amp_search(h, Q, k, nprobe, want_probes=True, **kw)
         compare_integer(g, oracle.search(idx, Q, k, nprobe, probes=g["probes"], **kw))
+
+
+# L1's row ranges: sixteen lanes per (pair, subspace) row, fewer rows than a
+# workgroup has groups of sixteen, and more
+@pytest.mark.parametrize("M,dsub", [(4, 8), (8, 4), (16, 5), (24, 2), (36, 3), (96, 2), (132, 1)])
+@pytest.mark.parametrize("bits", [4, 8, 12, 16, 0])
+def test_lane_classes_under_l1_are_bit_exact(M, dsub, bits):
+    idx = random_index(M + 9, M, dsub, nlist=12, n=1500, metric="l1")
+    h = amp.amp_index_from_arrays(idx)
+    r = np.random.default_rng(M + bits)
+    for nq, nprobe, k in ((1, 1, 5), (40, 5, 3)):
+        Q = (idx["centroids"][r.integers(1, 12, nq)] + r.standard_normal((nq, idx["d"]))).astype(np.float32)
+        kw = dict(policy="fixed", bits=bits)
+        if bits == 0:
+            kw = dict(policy="explicit", explicit_bits=r.choice(np.array([4, 8, 12, 16], np.uint8), size=(nq, nprobe)))
+        g = amp.amp_search(h, Q, k, nprobe, want_probes=True, **kw)
+        compare_integer(g, oracle.search(idx, Q, k, nprobe, probes=g["probes"], **kw))
