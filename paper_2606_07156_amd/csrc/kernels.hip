@@ -3020,9 +3020,10 @@ hipError_t launch_search(const amp_index* ix, const Workspace& ws, const float* 
       // FP8 build: every pair's LUT minima, as many pairs per workgroup as fit
       // 64 KB of residual rows (128 at most): they share the B fragments.  L1
       // shares nothing: 32 pairs, for enough workgroups to spread over the chip
-      // (700 queries, nprobe 32, M 16, d 80, whole searches with 128 / 64 / 32 /
-      // 16: alone 695 / 683 / 627 / 627 us, on three streams 450 / 432 / 406 /
-      // 410; M 96, 2000 queries, 5750 / 5745 / 5580 / 5660 alone)
+      // (whole searches with 32 / 128, us alone and on three streams: 700 queries,
+      // nprobe 32, M 16, d 80, 436 / 502 and 267 / 306; 8000, nprobe 16, M 16, d 64,
+      // 1535 / 1760 and 1264 / 1304; 2000, nprobe 32, d 64, 4 bits, 850 / 851 and
+      // 580 / 546; M 96, d 384, 3600 / 3757 and 3314 / 3488, there with 64)
       int G = sd.metric == AMP_L1 ? 32 : 128;
       while (G > 8 && (size_t)G * ri_stride(sd.d) * 2 > 65536) G >>= 1;
       ba.G = G;

@@ -140,7 +140,7 @@ __host__ __device__ inline ScanLds scan_lds_layout(int G, int wpr, int M, int d,
 // taken to the kernel's start and held over every unit: those on dsub, one per
 // dimension, in scalar registers that spill to vector lanes, which are read back
 // at each use (8-bit pairs in the mixed-class kernel, L1, M 16: 23 % more VALU
-// instructions, phase 2 513 us against 444 with a body less in the kernel).
+// instructions).
 __device__ __forceinline__ int local_scalar(int x) {
   asm volatile("" : "+s"(x));
   return x;
@@ -1601,8 +1601,8 @@ __global__ __launch_bounds__(NT, scan_min_blocks(MT, NT))
 // pairs per unit) serves every class.  GRAN: quantiser granularity, whose classes
 // alone the kernel holds (three bodies; with both granularities' it took 48 bytes
 // of scratch per lane at M 24, 80 at M 120, 128 at M 128, and now none, none and
-// 48; whole searches, 2000 queries, with both / now: L1 M 16 1061 / 964 us, L2
-// M 16 183 / 172, M 40 515 / 502, inner product M 128 769 / 751).
+// 48; whole searches, 2000 queries, us with both / now: L2 M 16 183 / 172, M 40
+// 515 / 502, inner product M 128 769 / 751).
 template <int MT, int PHASE, int DT, int NR, int NT, int GRAN>
 __global__ __launch_bounds__(NT, scan_min_blocks(MT, NT))
     __attribute__((amdgpu_waves_per_eu(NT / 64 * scan_min_blocks(MT, NT) / 4, NT == 512 ? 2 : 8))) void k_scan_mix(ScanArgs a) {
